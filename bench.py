@@ -76,17 +76,17 @@ def kernel_sources_sha256():
 
 def exact_peak_mac_s(cl):
     """Emulation ceiling of one exact-mode multiply-accumulate: gfx950 has no
-    adder for the paper's FP16, so a MAC costs at least one FP32 FMA plus
-    three more VALU ops that round the result to a 10-bit significand, and
-    each chunk end adds one more add + rounding (4 ops) per output.  Priced at
+    adder for the paper's FP16, so a MAC costs one FP32 FMA plus two more VALU
+    ops that round the result to a 10-bit significand, and each chunk end
+    adds one more add + rounding (3 ops) per output.  Priced at
     the chip's full VALU rate."""
-    return VALU_LANE_OPS / (4.0 + 4.0 / cl)
+    return VALU_LANE_OPS / (3.0 + 3.0 / cl)
 
 
 def fast_peak_mac_s(cl):
-    """Fast mode: min(FP8 MFMA peak, VALU epilogue of 8 ops per output per
-    chunk: scale, round, add, round)."""
-    return min(FP8_MFMA_MAC_S, VALU_LANE_OPS * cl / 8.0)
+    """Fast mode: min(FP8 MFMA peak, VALU epilogue of 6 ops per output per
+    chunk: round (2), add, round (2), running maximum)."""
+    return min(FP8_MFMA_MAC_S, VALU_LANE_OPS * cl / 6.0)
 
 
 def sr_gemm_peak_mac_s():

@@ -133,16 +133,24 @@ __device__ __forceinline__ uint32_t fp16_code(float x) {
     else return f32d_to_fp16<DOM>(x);
 }
 
-// Round to a 10-bit significand, ties to even, by Veltkamp splitting
-// (c = x (2^14 + 1), hi = c - (c - x)): three full-rate VALU operations.
-// Valid when x (2^14 + 1) neither overflows nor leaves the normal range --
-// for the GEMM's guarded path (|x| in [2^-39, 2^31] or 0) it always holds.
-// Equality with integer round-to-nearest-even is checked exhaustively over
-// whole binades of both signs in the tests.
+// Round to a 10-bit significand, ties to even, in two full-rate VALU
+// operations: s = RN(x (1 - 2^14)), hi = fma(x, 2^14, s).  With G = 2^14
+// ulp(x) and X = x / ulp(x) (an integer of 24 bits), 2^14 x is X G and s the
+// multiple of ulp(s) nearest to -(X - X / 2^14) G, so hi = (X - RN(X - X /
+// 2^14)) G, which the FMA forms exactly.  ulp(s) is G wherever |s| stays in
+// the binade of X G: everywhere but for X below 2^23 + 2^9, where it is G / 2
+// -- but there X / 2^14 lies within 2^-5 of 2^9, whose multiple of G / 2 is
+// 2^9 G itself.  Elsewhere hi is X / 2^14 rounded to an integer; in a tie X is
+// a multiple of 2^13, hence even, so s's even neighbour is hi's even neighbour.
+// (Subtracting is what makes it exact: with 1 + 2^14 the sum can leave the
+// binade at its top, where ulp(s) doubles.)  Valid while x 2^14 does not
+// overflow and x / 2^14 stays normal -- for the guarded paths (|x| in [2^-39,
+// 2^31] or 0) always; zero gives +0.  Equality with integer
+// round-to-nearest-even is checked exhaustively over whole binades of both
+// signs in the tests.
 __device__ __forceinline__ float rn16v(float x) {
-    const float c = x * 16385.0f;
-    const float d = c - x;
-    return c - d;
+    const float s = x * -16383.0f;
+    return __builtin_fmaf(x, 16384.0f, s);
 }
 
 // A product of two FP16 values rounded to FP16, nearest even (Sec. 2.3 /

@@ -9,7 +9,7 @@
 // short chunks (CL = 8: K/8 chunk sums per output) or one chunk (CL >= K)
 // that is impossible or costs far more memory traffic than the arithmetic,
 // so the chip's parallelism has to come from the outputs alone: a 512 x 512
-// output is 262144 chains.  Each chain step is an FMA and a three-instruction
+// output is 262144 chains.  Each chain step is an FMA and a two-instruction
 // rounding, each depending on the last, so a SIMD needs several waves (or
 // several chains per lane) in flight to issue every cycle; with few outputs
 // the kernel keeps few chains per lane -- TM x TN of 1 x 1, 1 x 2 or 2 x 2,
@@ -19,8 +19,8 @@
 // one 16-byte read gives a lane 4 consecutive k of a row; the reads of the
 // next 4 k are issued before the arithmetic of the current 4, and K slabs of
 // 64 are double-buffered from HBM.  Per multiply-accumulate it issues the FMA
-// and the rounding of the exact-mode kernels (guarded: plain values,
-// Veltkamp; safe: scaled by 2^96, integer rounding, for tiles that fail the
+// and the rounding of the exact-mode kernels (guarded: plain values, a
+// multiplication and an FMA; safe: scaled by 2^96, integer rounding, for tiles that fail the
 // overflow guard), with the same bits.  FAST: a chunk is summed in plain FP32
 // (one FMA per multiply-accumulate) and rounded to FP16 once at its end, then
 // added into the running sum in the 2^96 domain -- the arithmetic of the

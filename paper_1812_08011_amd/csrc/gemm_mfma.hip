@@ -16,7 +16,7 @@
 // epilogue rounds it and adds it into S.  The epilogue dominates (at CL = 64
 // the matrix cores finish a chunk several times faster than the VALU rounds
 // it), so two epilogues exist, as in the exact mode:
-//   * guarded: plain values, Veltkamp rounding (rn16v), 9 full-rate VALU ops
+//   * guarded: plain values, rounding by rn16v, 6 full-rate VALU ops
 //     per output per chunk including a running max of |p| and |S|; a piece in
 //     which any value reached 2^32 (where FP16 would overflow to Inf) is
 //     recomputed with
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(kNT) void chunk_gemm_mfma(GemmArgs g, Plan p) {
                         if (SAFE) {
                             pv = rn16s(acc[i][j][r] * 0x1p96f);
                         } else {
-                            // Veltkamp rounding turns an Inf sum into NaN
+                            // rn16v turns an Inf sum into NaN
                             pv = rn16v(acc[i][j][r]);
                             nonfinite |= !(fabsf(pv) < 2147483648.0f);
                         }

@@ -24,7 +24,7 @@
 //     while the current one is consumed; with every step interior and 16-byte
 //     aligned (AL) there is one load path, so the compiler waits for one set
 //     only; the workgroup streams on across its tiles;
-//   * the guarded epilogue (plain values, Veltkamp rounding, running max of
+//   * the guarded epilogue (plain values, rn16v, running max of
 //     |p| -- taken by the wave that rounds p -- and of |S|) runs in the
 //     stream; a tile in which a value reached 2^32 (FP16 overflow) is
 //     remembered and recomputed after the stream with the

@@ -5,7 +5,7 @@
 // operands bf8 (the FP8 codes are OCP E5M2 = bf8), rounded to FP16 once, and added into the running sum
 // in ascending chunk order with FP16 rounding after every add.  The design
 // differs in how the work reaches the matrix cores and the VALU:
-//   * the register budget allows 4 waves per SIMD (the VALU epilogue, 8
+//   * the register budget allows 4 waves per SIMD (the VALU epilogue, 6
 //     full-rate instructions per output per chunk, is the bound; the matrix
 //     cores and the memory pipeline need other waves to hide behind);
 //   * the workgroup's work items (whole tiles, then its share of the split
@@ -13,10 +13,10 @@
 //     slabs: the next slab -- of the same piece or the next one -- is loaded
 //     from memory while the current one is consumed, so short pieces (K of a
 //     few chunks) do not pay the memory latency once per tile;
-//   * only the guarded epilogue (plain values, Veltkamp rounding, running
+//   * only the guarded epilogue (plain values, rn16v, running
 //     max of |S| at chunk ends) runs in the stream.  A piece in which a
 //     running sum reached 2^31 (so a chunk sum or sum may have overflowed
-//     FP16) or ended NaN (Inf operands: Veltkamp rounding of Inf gives NaN,
+//     FP16) or ended NaN (Inf operands: rn16v of Inf gives NaN,
 //     which stays) is remembered and recomputed after the stream with the
 //     2^96-scaled epilogue (integer rounding on raw bits), which gives the
 //     same bits wherever the guarded one is valid.
@@ -226,7 +226,7 @@ void chunk_gemm_mfma_stream(GemmArgs g, Plan p) {
                 if (SAFE) {
                     pv = rn16s(acc[r] * 0x1p96f);
                 } else {
-                    // Veltkamp rounding turns an Inf sum into NaN
+                    // rn16v turns an Inf sum into NaN
                     pv = rn16v(acc[r]);
                     nonfinite |= !(fabsf(pv) < 2147483648.0f);
                 }

@@ -2,6 +2,7 @@
 single precision (numpy float32 arithmetic rounds to nearest even, as the
 VALU does).  These pin the device algorithms, not the oracle."""
 import numpy as np
+import pytest
 
 
 def rne_significand10(u):
@@ -39,6 +40,40 @@ def test_veltkamp_split_keeps_short_values():
         assert np.array_equal(veltkamp10(x), x)
         assert np.array_equal(veltkamp10(-x), -x)
     assert veltkamp10(np.float32([0.0]))[0] == 0.0
+
+
+def two_step10(x):
+    """s = x (1 - 2^14) rounded to float32; hi = fma(x, 2^14, s).  Returns hi
+    after checking that the float64 value of the FMA is exact in float32."""
+    s = (x * np.float32(-16383.0)).astype(np.float32)
+    exact = x.astype(np.float64) * 16384.0 + s.astype(np.float64)
+    hi = exact.astype(np.float32)
+    assert np.array_equal(hi.astype(np.float64), exact)
+    return hi
+
+
+@pytest.mark.parametrize("e", [-39, -30, -1, 0, 30, 62])
+def test_two_step_rounding_is_round_to_nearest_even_on_whole_binades(e):
+    """The GEMMs' guarded rounding (a multiplication and an FMA), exhaustive
+    over every significand of a binade and both signs: the bits of integer
+    round-to-nearest-even.  Binades from FP16's smallest step to beyond the
+    largest sum a guarded piece can hold (2^31 products of 2^31.6)."""
+    m = np.arange(1 << 23, dtype=np.uint32)
+    for sign in (0, 1):
+        u = (np.uint32(sign) << np.uint32(31)) | (np.uint32(127 + e) << np.uint32(23)) | m
+        assert np.array_equal(two_step10(u.view(np.float32)).view(np.uint32),
+                              rne_significand10(u))
+
+
+def test_two_step_rounding_keeps_short_values_and_zero():
+    """Values with at most 10 significant bits (FP16 subnormal sums among
+    them) pass through; either zero gives +0."""
+    k = np.arange(1, 1 << 10, dtype=np.float64)
+    for scale in (2.0 ** -39, 2.0 ** -20, 2.0 ** 10):
+        x = (k * scale).astype(np.float32)
+        assert np.array_equal(two_step10(x), x)
+        assert np.array_equal(two_step10(-x), -x)
+    assert np.all(two_step10(np.float32([0.0, -0.0])).view(np.uint32) == 0)
 
 
 # --- products of two FP16 values (the FP16-operand GEMM) -------------------
