@@ -283,6 +283,31 @@ __device__ __forceinline__ u32x4 philox4x32_10(u32x4 c, uint32_t k0, uint32_t k1
     return c;
 }
 
+// A wave-uniform value held in a vector register: on gfx950 a vector
+// instruction that reads a scalar register issues at half rate (measured: 28.7
+// against 50 T lane-instructions/s for v_xor_b32), so values that a hot loop
+// reads on the vector ALUs are copied once.
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t s) {
+    uint32_t v;
+    asm("v_mov_b32 %0, %1" : "=v"(v) : "s"(s));
+    return v;
+}
+
+// a ^ b ^ c and ~(a ^ b ^ c), every operand in vector registers (full rate).
+__device__ __forceinline__ uint32_t xor3_vvv(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ uint32_t xnor3_vvv(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x69" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+constexpr uint32_t kPhiloxM0 = 0xD2511F53u, kPhiloxM1 = 0xCD9E8D57u;
+constexpr uint32_t kPhiloxW0 = 0x9E3779B9u, kPhiloxW1 = 0xBB67AE85u;
+
 // Stochastic rounding of a plain float into FP16 (Eq. (1), k' = 23, k = 9):
 // round the magnitude up by one step with probability F / 2^16, where F is
 // the discarded fraction of a step scaled to 16 bits; u16 is uniform on

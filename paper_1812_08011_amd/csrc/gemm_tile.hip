@@ -36,6 +36,8 @@
 
 #include <stdio.h>
 
+#include <type_traits>
+
 namespace fp8t {
 namespace {
 
@@ -77,6 +79,82 @@ __device__ __forceinline__ u32x4 block_of(uint32_t i, uint32_t j, uint32_t q, ui
     return philox4x32_10(c, g.k0, g.k1);
 }
 
+// The uniforms of a thread's 4 x 4 outputs for products k = 2 kq, 2 kq + 1:
+// Philox blocks (i + r, j4, kq, w3), r = 0 .. 3, complemented.  The first
+// three rounds share most of their work between the blocks of a thread and
+// between its k: with round q's products p0 = M0 x, p1 = M1 z,
+//   round 1: p0 = M0 (i + r) does not depend on k, p1 = M1 kq is wave-uniform;
+//   round 2: p0 = M0 x is the same for the four rows (x = hi(M1 kq) ^ j4 ^ key),
+//            p1 = M1 z does not depend on k (z = hi(M0 (i + r)) ^ w3 ^ key);
+//   round 3 xors with values of the row or of k alone.
+// What depends on the row alone is computed once per tile (RowBits), so four
+// blocks take 65 multiplications instead of 80.  The keys of rounds 4 .. 10
+// are held in vector registers: the three-input xor issues at half rate with
+// a scalar operand.  Bound by the vector ALUs: about 5.8 full-rate slots of
+// Philox per multiply-accumulate and 4.5 for the sum.  Measured, 512 x 512
+// outputs, K 4096: 346 -> 278 us, most of it from four waves per SIMD (the
+// chunk end outside the loop over k) instead of two.
+struct LateKeys {
+    uint32_t a[7], b[7];              // keys of rounds 4 .. 10
+    __device__ __forceinline__ explicit LateKeys(const TileArgs& g) {
+#pragma unroll
+        for (uint32_t r = 0; r < 7; ++r) {
+            a[r] = in_vgpr(g.k0 + (r + 3) * kPhiloxW0);
+            b[r] = in_vgpr(g.k1 + (r + 3) * kPhiloxW1);
+        }
+    }
+};
+
+struct RowBits {
+    uint32_t jk;                      // j4 ^ key of round 1
+    uint32_t hz[kT];                  // hi(M1 z) of round 2
+    uint32_t lz[kT];                  // lo(M1 z) of round 2 ^ round 3's first key
+    uint32_t lx[kT];                  // lo(M0 (i + r)) of round 1 ^ round 2's second key
+    __device__ __forceinline__ RowBits(uint32_t i, uint32_t j4, const TileArgs& g) {
+        jk = j4 ^ g.k0;
+#pragma unroll
+        for (uint32_t r = 0; r < kT; ++r) {
+            const uint64_t p0 = (uint64_t)kPhiloxM0 * (i + r);
+            const uint32_t z = (uint32_t)(p0 >> 32) ^ g.w3 ^ g.k1;
+            const uint64_t p1 = (uint64_t)kPhiloxM1 * z;
+            hz[r] = (uint32_t)(p1 >> 32);
+            lz[r] = (uint32_t)p1 ^ (g.k0 + 2u * kPhiloxW0);
+            lx[r] = (uint32_t)p0 ^ (g.k1 + kPhiloxW1);
+        }
+    }
+    // kq wave-uniform
+    __device__ __forceinline__ void blocks(uint32_t kq, const LateKeys& key, const TileArgs& g,
+                                           uint32_t (&nw)[kT][4]) const {
+        const uint64_t u = (uint64_t)kPhiloxM1 * kq;                    // round 1, uniform
+        const uint32_t yk = in_vgpr((uint32_t)u ^ (g.k0 + kPhiloxW0));
+        const uint64_t s = (uint64_t)kPhiloxM0 * (jk ^ (uint32_t)(u >> 32));   // round 2, shared
+        const uint32_t sh = (uint32_t)(s >> 32);
+        const uint32_t sl = (uint32_t)s ^ (g.k1 + 2u * kPhiloxW1);
+#pragma unroll
+        for (int r = 0; r < kT; ++r) {
+            uint64_t p0 = (uint64_t)kPhiloxM0 * (hz[r] ^ yk);           // round 3
+            uint64_t p1 = (uint64_t)kPhiloxM1 * (sh ^ lx[r]);
+            uint32_t x = (uint32_t)(p1 >> 32) ^ lz[r], y = (uint32_t)p1;
+            uint32_t z = (uint32_t)(p0 >> 32) ^ sl, w = (uint32_t)p0;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {                               // rounds 4 .. 9
+                p0 = (uint64_t)kPhiloxM0 * x;
+                p1 = (uint64_t)kPhiloxM1 * z;
+                x = xor3_vvv((uint32_t)(p1 >> 32), y, key.a[q]);
+                y = (uint32_t)p1;
+                z = xor3_vvv((uint32_t)(p0 >> 32), w, key.b[q]);
+                w = (uint32_t)p0;
+            }
+            p0 = (uint64_t)kPhiloxM0 * x;                               // round 10
+            p1 = (uint64_t)kPhiloxM1 * z;
+            nw[r][0] = xnor3_vvv((uint32_t)(p1 >> 32), y, key.a[6]);
+            nw[r][1] = ~(uint32_t)p1;
+            nw[r][2] = xnor3_vvv((uint32_t)(p0 >> 32), w, key.b[6]);
+            nw[r][3] = ~(uint32_t)p0;
+        }
+    }
+};
+
 // Stage a whole slab (64 rows x 32 k, all inside the matrix, aligned rows)
 // with one 8-byte load per thread, A scaled by 2^96, B plain.  KC: k is
 // contiguous in memory (element (r, k) at p[r * ld + k]); otherwise the row
@@ -113,13 +191,15 @@ __device__ __forceinline__ void stage_fast(const uint8_t* __restrict__ p, int64_
 // One launch of the persistent plan: workgroup w takes whole tiles w, w + G,
 // ..., then its range of the shared tile-chunks.
 template <bool TA, bool TB>
-__global__ __launch_bounds__(kNT) void chunk_gemm_sr_kernel(TileArgs g, Plan p) {
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4)))
+void chunk_gemm_sr_kernel(TileArgs g, Plan p) {
     const uint8_t* __restrict__ A = g.A;
     const uint8_t* __restrict__ B = g.B;
     __shared__ __attribute__((aligned(16))) float As[kBK][kPitch];
     __shared__ __attribute__((aligned(16))) float Bs[kBK][kPitch];
     const int tid = threadIdx.x;
     const int tx = tid % kTiles, ty = tid / kTiles;
+    const LateKeys keys(g);
 
     // chunks [c0, c1) of tile; lt >= 0 for a shared tile
     auto piece = [&](int64_t tile, int c0, int c1, int64_t lt) __attribute__((always_inline)) {
@@ -132,6 +212,7 @@ __global__ __launch_bounds__(kNT) void chunk_gemm_sr_kernel(TileArgs g, Plan p) 
         const int kend = kend64 < g.K ? (int)kend64 : g.K;
         const bool to_ws = c0 > 0;
         const uint32_t gi = (uint32_t)(m0 + ty * kT), gj = (uint32_t)(n0 + tx * kT);
+        const RowBits bits(gi, gj >> 2, g);
         float P[kT][kT], S[kT][kT];
 #pragma unroll
         for (int r = 0; r < kT; ++r)
@@ -210,34 +291,35 @@ __global__ __launch_bounds__(kNT) void chunk_gemm_sr_kernel(TileArgs g, Plan p) 
                 }
             }
             __syncthreads();
+            // up to the chunk's end or the slab's: two k per set of blocks (the
+            // chunk end outside that loop: inside it, its registers kept the
+            // kernel at two waves per SIMD)
+            for (int kseg = lo; kseg < hi;) {
+                const int kstop = cend < hi ? (int)cend : hi;
 #pragma unroll 1
-            for (int gq = lo & ~1; gq < hi; gq += 2) {
-                // rows' blocks for k = gq, gq + 1 (complemented words)
-                uint32_t nw[kT][4];
+                for (int gq = kseg & ~1; gq < kstop; gq += 2) {
+                    // rows' blocks for k = gq, gq + 1 (complemented words)
+                    uint32_t nw[kT][4];
+                    bits.blocks((uint32_t)(gq >> 1), keys, g, nw);
+                    auto product = [&](auto half) __attribute__((always_inline)) {
+                        constexpr int s = decltype(half)::value;
+                        const int k = gq + s;
+                        const float4 a4 = *reinterpret_cast<const float4*>(&As[k - sb][ty * kT]);
+                        const float4 b4 = *reinterpret_cast<const float4*>(&Bs[k - sb][tx * kT]);
+                        const float av[4] = {a4.x, a4.y, a4.z, a4.w};
+                        const float bv[4] = {b4.x, b4.y, b4.z, b4.w};
 #pragma unroll
-                for (int r = 0; r < kT; ++r) {
-                    const u32x4 b = block_of(gi + r, gj >> 2, (uint32_t)(gq >> 1), g.w3, g);
-                    nw[r][0] = ~b.x;
-                    nw[r][1] = ~b.y;
-                    nw[r][2] = ~b.z;
-                    nw[r][3] = ~b.w;
+                        for (int r = 0; r < kT; ++r)
+#pragma unroll
+                            for (int c = 0; c < kT; ++c)
+                                P[r][c] = sr16s(__builtin_fmaf(av[r], bv[c], P[r][c]),
+                                                sr_addend(nw[r][2 * s + c / 2], c % 2));
+                    };
+                    if (gq >= kseg) product(std::integral_constant<int, 0>{});
+                    if (gq + 1 < kstop) product(std::integral_constant<int, 1>{});
                 }
-#pragma unroll
-                for (int s = 0; s < 2; ++s) {
-                    const int k = gq + s;
-                    if (k < lo || k >= hi) continue;
-                    const float4 a4 = *reinterpret_cast<const float4*>(&As[k - sb][ty * kT]);
-                    const float4 b4 = *reinterpret_cast<const float4*>(&Bs[k - sb][tx * kT]);
-                    const float av[4] = {a4.x, a4.y, a4.z, a4.w};
-                    const float bv[4] = {b4.x, b4.y, b4.z, b4.w};
-#pragma unroll
-                    for (int r = 0; r < kT; ++r)
-#pragma unroll
-                        for (int c = 0; c < kT; ++c)
-                            P[r][c] = sr16s(__builtin_fmaf(av[r], bv[c], P[r][c]),
-                                            sr_addend(nw[r][2 * s + c / 2], c % 2));
-                    if (k + 1 == cend) chunk_end();
-                }
+                kseg = kstop;
+                if (kstop == cend) chunk_end();
             }
         }
         if (to_ws) return;

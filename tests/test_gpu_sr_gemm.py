@@ -123,3 +123,15 @@ def test_sr_gemm_padded_leading_dims():
     say("chunk_gemm_sr padded leading dimensions")
     fp8t.chunk_gemm_sr(0, 0, M, N, K, CL, dev(Ap), K + 5, dev(Bp), N + 3, C, N + 1, 9, 1)
     assert np.array_equal(host(C)[:, :N], oracle.chunk_gemm_sr(A, B, CL, seed=9, offset=1))
+
+
+@pytest.mark.parametrize("seed,offset", [(2 ** 64 - 3, 2 ** 31 - 1), (2 ** 33 + 5, 0)])
+@pytest.mark.parametrize("CL", [9, 32])
+def test_sr_gemm_key_schedule_extremes(seed, offset, CL):
+    """Keys that wrap in every round and chunk ends on either product of a
+    pair that shares its random blocks, rows and columns beyond a tile."""
+    M, N, K = 67, 69, 131
+    A, B = operands(np.random.default_rng(77), M, N, K, 0, 0, scale=4.0)
+    say(f"chunk_gemm_sr keys seed={seed} offset={offset} CL={CL}")
+    got = sr_gemm(dev(A), dev(B), M, N, K, CL, 0, 0, seed, offset)
+    assert np.array_equal(got, oracle.chunk_gemm_sr(A, B, CL, seed=seed, offset=offset))
