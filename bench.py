@@ -57,7 +57,8 @@ EXACT_TRAFFIC_BYTES_PER_CALL = 963.8e6
 # The sources that decide what an exact-mode chunk_gemm call runs: the VALU
 # kernel, its instantiations, the planner and fold pass, the shared device code.
 EXACT_KERNEL_SOURCES = ("chunk_gemm.hip", "fp8t_device.h", "fp8t_host.h", "gemm_plan.h",
-                        "gemm_chain.hip", "gemm_valu.h", "gemm_valu.hip", "gemm_valu_impl.h",
+                        "gemm_chain.hip", "gemm_cpar_impl.h", "gemm_cpar_nn.hip",
+                        "gemm_cpar_nt.hip", "gemm_cpar_tn.hip", "gemm_cpar_tt.hip", "gemm_valu.h", "gemm_valu.hip", "gemm_valu_impl.h",
                         "gemm_valu_nn.hip", "gemm_valu_nt.hip", "gemm_valu_tn.hip",
                         "gemm_valu_tt.hip")
 

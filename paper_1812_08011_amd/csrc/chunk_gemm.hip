@@ -213,41 +213,62 @@ constexpr double kLanesPerCU = 128.0;   // 32-bit VALU lane-ops per clock per CU
 constexpr double kFoldBytesPerS = 5e12; // effective HBM rate of the fold pass
 
 // Relative cost per multiply-accumulate of each register tile on a CU with
-// enough waves resident (see valu_efficiency), in VALU instructions (4 for
-// the rounded FMA of the guarded path, plus operand decode, LDS reads and
-// loop overhead; measured on the conv-stage GEMMs for the large tiles, on
-// the 512 x 512 long-accumulation GEMMs for the small ones).
+// enough waves resident (see valu_efficiency), in VALU instructions at the
+// peak clock: 3 for the rounded FMA of the guarded path, plus operand decode,
+// LDS reads, loop overhead and the clock the chip holds; from the times of the
+// 50176 x 256 x 2304 GEMM (large tiles) and the 512 x 512 x 16384 one (small
+// tiles, and the chunk-per-wave kernel).
 double valu_ops_per_mac(int cfg) {
     switch (cfg) {
-        case 4: return 4.6;     // 4 x 4, 4 waves per SIMD
-        case 3: return 4.85;    // 4 x 8
-        case 2: return 4.9;     // 8 x 4
-        case 1: return 5.1;     // 8 x 8, 2 waves per SIMD
-        case 0: return 5.2;
-        case 7: return 4.3;     // 4 x 4 on 128 x 64 tiles, 8 waves per workgroup
-        case 8: return 4.3;     // 4 x 4 on 64 x 128 tiles, 8 waves per workgroup
-        case 5: return 7.0;     // 2 x 2
-        case kChainConfig: return 6.0;       // chain kernel, 2 x 2
-        case kChainConfig + 1: return 6.1;   // chain kernel, 1 x 2
-        case kChainConfig + 2: return 9.0;   // chain kernel, 1 x 1
+        case 4: return 4.3;     // 4 x 4, 4 waves per SIMD
+        case 3: return 4.65;    // 4 x 8
+        case 2: return 4.6;     // 8 x 4
+        case 1: return 4.8;     // 8 x 8, 2 waves per SIMD
+        case 0: return 4.9;
+        case 7: return 3.97;    // 4 x 4 on 128 x 64 tiles, 8 waves per workgroup
+        case 8: return 3.95;    // 4 x 4 on 64 x 128 tiles, 8 waves per workgroup
+        case 5: return 5.5;     // 2 x 2
+        case kCparConfig:       // a chunk per wave, 4 x 4
+        case kCparConfig + 1:
+        case kCparConfig + 2: return 4.4;
+        case kCparConfig + 3:   // 2 x 2
+        case kCparConfig + 4:
+        case kCparConfig + 5: return 5.95;
+        case kChainConfig: return 5.6;       // chain kernel, 2 x 2
+        case kChainConfig + 1: return 6.2;   // chain kernel, 1 x 2
+        case kChainConfig + 2: return 7.8;   // chain kernel, 1 x 1
         default: return 10.8;   // 1 x 1
     }
 }
 
-// Fraction of a CU's VALU rate reached with w waves per SIMD resident: each
-// multiply-accumulate is a chain of four dependent instructions, and on
-// gfx950 about four waves per SIMD are needed to issue every cycle whatever
-// the outputs per lane (measured: a 2 x 2 register tile at one wave per SIMD
-// runs at a quarter of the rate a 1 x 1 tile reaches at four).
 // VALU instructions per multiply-accumulate the fast chain kernel saves over
 // the exact one (measured on 512 x 512 outputs, K 16384 and 65536, CL 8 and
 // 12): the rounding after each FMA goes, worth more on the 2 x 2 tile than
 // on the narrower ones.
 double chain_fast_saving(int cfg) {
-    return cfg == kChainConfig ? 3.0 : cfg == kChainConfig + 1 ? 2.3 : 2.6;
+    return cfg == kChainConfig ? 2.6 : cfg == kChainConfig + 1 ? 2.4 : 1.4;
 }
 
+// Fraction of a CU's VALU rate reached with w waves per SIMD resident: each
+// multiply-accumulate is a chain of dependent instructions, and on gfx950
+// about four waves per SIMD are needed to issue every cycle (measured with a
+// barrier per slab: a 2 x 2 register tile at one wave per SIMD runs at a
+// quarter of the rate a 1 x 1 tile reaches at four).  The chunk-per-wave
+// kernel has no such barrier and issues better with few waves (measured: 256 x
+// 1024 x 1024 with 4 x 4 tiles 34 / 21 / 20 us at one / two / four, 128 x 128
+// x 1024 with 2 x 2 tiles 14.4 / 9.7 / 9.0 us).
 double valu_efficiency(double w) { return w >= 4.0 ? 1.0 : w / 4.0; }
+double cpar_efficiency(double w) {
+    return w >= 4.0 ? 1.0 : w >= 2.0 ? 0.92 + 0.04 * (w - 2.0) : 0.52 + 0.4 * (w - 1.0);
+}
+// A chunk-per-wave tile's start and end (operand latency, result stores): the
+// more waves a workgroup has, the fewer workgroups a CU holds to cover them.
+double cpar_cost_per_tile(int waves) { return waves == 4 ? 0.5e-6 : waves == 8 ? 0.7e-6 : 1.2e-6; }
+
+// The fold pass of the VALU kernels' shared tiles: a fixed part (launch, the
+// pieces' starts) and the chunk sums written and read back (measured: 27 us
+// for 134 MB of them, 170 us for 0.8 GB, 6-9 us where there are few).
+constexpr double kValuFoldFixed = 9e-6, kValuFoldBytesPerS = 1e13;
 
 // Extra VALU instructions per multiply-accumulate with FP16 operands: the
 // product's multiplication and its rounding to FP16 (and, max, add and the
@@ -342,6 +363,8 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
             } else {
                 // the chain kernel: 4-k groups inside one chunk
                 if (is_chain(cfg) && (conv || p16 || (CL % 4 != 0 && CL < K))) continue;
+                if (is_cpar(cfg) && (conv || p16 || fast || CL < 32 || K < 32 || M < 16 || N < 16))
+                    continue;
                 const ValuShape sh = valu_shape(cfg);
                 fn = conv ? valu_conv_kernel(cfg, ta)
                    : p16  ? valu_p16_kernel(cfg, ta, tb)
@@ -355,6 +378,9 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
                 t_out = ((double)CL * ops + 4.0) / (kLanesPerCU * kClockHz);
             }
             if (!fn) continue;
+            const bool cpar = !mf && is_cpar(cfg);
+            const int nw = cpar ? cpar_waves(cfg) : 1;
+            if (cpar) t_tile = cpar_cost_per_tile(nw);
             int occ = kernel_occupancy(fn, NT);
             if (occ <= 0) continue;
             if (occ > 8) occ = 8;
@@ -402,7 +428,12 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
                     int64_t per_cu = (T + cus - 1) / cus;
                     if (mf && cfg == 2 && per_cu < 2) per_cu = 2;
                     est = (double)per_cu * (nch * t_chunk + t_tile);
-                    if (!mf) {
+                    if (cpar) {
+                        // rounds of nw chunks
+                        const int64_t res = per_cu < occ ? per_cu : occ;
+                        est = (double)per_cu * ((nch + nw - 1) / nw * nw * t_chunk /
+                                                cpar_efficiency((double)res * NT / 256.0) + t_tile);
+                    } else if (!mf) {
                         const int64_t res = per_cu < occ ? per_cu : occ;
                         est /= valu_efficiency((double)res * NT / 256.0);
                     }
@@ -419,11 +450,19 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
                     ws = (size_t)(T - p.t_whole) * nch * BM * BN * sizeof(uint16_t) + kWsAlign;
                     if (ws > ws_cap) continue;
                     est = (double)wg_per_cu * (per_wg * t_chunk + (q + 2) * t_tile);
-                    if (!mf) {
+                    if (cpar) {
+                        const int64_t rest = (p.L + G - 1) / G;
+                        const double chunks = (double)(q * ((nch + nw - 1) / nw * nw)) +
+                                              (double)(rest > nw / 2 ? rest : nw / 2);
+                        const int64_t res = wg_per_cu < occ ? wg_per_cu : occ;
+                        est = (double)wg_per_cu * (chunks * t_chunk /
+                              cpar_efficiency((double)res * NT / 256.0) + (q + 2) * t_tile);
+                    } else if (!mf) {
                         const int64_t res = wg_per_cu < occ ? wg_per_cu : occ;
                         est /= valu_efficiency((double)res * NT / 256.0);
                     }
-                    est += 2.0 * (double)ws / kFoldBytesPerS + 4e-6;
+                    est += mf ? 2.0 * (double)ws / kFoldBytesPerS + 4e-6
+                              : 2.0 * (double)ws / kValuFoldBytesPerS + kValuFoldFixed;
                 }
                 p.xcd_remap = p.t_whole % 8 == 0 && p.G % 8 == 0;
                 if (force_split == 1 && !split && allow_ws) est *= 1e6;   // any shared plan wins

@@ -190,6 +190,14 @@ __device__ __forceinline__ float max3_abs(float m, float a, float b) {
     return r;
 }
 
+// max(m, |a|, |b|) with NaN propagating (IEEE 754-2019 maximum): any NaN
+// operand gives NaN.
+__device__ __forceinline__ float maximum3_abs(float m, float a, float b) {
+    float r;
+    asm("v_maximum3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(m), "v"(a), "v"(b));
+    return r;
+}
+
 // Plain float -> nearest FP16 code, ties to even; overflow -> Inf.
 __device__ __forceinline__ uint16_t f32_to_fp16_rn(float x) {
     uint32_t u = __float_as_uint(x);

@@ -55,14 +55,6 @@ __device__ __forceinline__ int seg_off(int r, int g) { return r * kP + 16 * (g ^
 typedef __attribute__((address_space(1))) const void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
-// max(m, |a|, |b|) with NaN propagating (IEEE 754-2019 maximum): any NaN
-// operand gives NaN.
-__device__ __forceinline__ float maximum3_abs(float m, float a, float b) {
-    float r;
-    asm("v_maximum3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(m), "v"(a), "v"(b));
-    return r;
-}
-
 // Orders a wave's LDS accesses across its lanes: the LDS executes one wave's
 // instructions in order, and the fences keep the compiler from moving
 // accesses across.

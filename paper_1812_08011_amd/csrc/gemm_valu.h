@@ -15,9 +15,15 @@ struct ValuShape {
 // Configurations 0-8 are chunk_gemm_valu register tiles (gemm_valu_impl.h);
 // configurations 9, 10, 11 are chunk_gemm_chain (gemm_chain.hip) with 2 x 2,
 // 1 x 2 and 1 x 1 outputs per lane: whole tiles, CL a multiple of 4 or
-// covering K.
-constexpr int kValuConfigs = 12;
+// covering K; configurations 12-17 are chunk_gemm_cpar (gemm_cpar_impl.h), a
+// chunk per wave: 4 x 4 outputs per lane with 4, 8 or 16 waves per tile, then
+// 2 x 2.
+constexpr int kValuConfigs = 18;
 constexpr int kChainConfig = 9;
+constexpr int kCparConfig = 12;
+inline bool is_cpar(int cfg) { return cfg >= kCparConfig && cfg < kValuConfigs; }
+// Waves of a chunk_gemm_cpar workgroup: they take consecutive chunks of its tile.
+inline int cpar_waves(int cfg) { return 4 << (cfg - kCparConfig) % 3; }
 inline bool is_chain(int cfg) { return cfg >= kChainConfig && cfg < kChainConfig + 3; }
 
 ValuShape valu_shape(int cfg);
