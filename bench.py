@@ -102,11 +102,11 @@ def sr_gemm_peak_mac_s():
 
 def p16_peak_mac_s(cl):
     """ALU ceiling of chunk_gemm_p16 (FP16 operands): per multiply-accumulate
-    the product's Veltkamp rounding to FP16 (a multiply by the pre-split
-    operand, an FMA and an add), the add into the chunk sum and its rounding
-    (multiply, subtract, subtract): 7 VALU ops, plus the chunk end's 4 per
-    output.  Priced at the chip's full VALU rate."""
-    return VALU_LANE_OPS / (7.0 + 4.0 / cl)
+    the product's rounding to FP16 (a multiply by the pre-split operand and an
+    FMA), the add into the chunk sum and its rounding (multiply, FMA): 5 VALU
+    ops, plus the chunk end's 3 per output.  Priced at the chip's full VALU
+    rate."""
+    return VALU_LANE_OPS / (5.0 + 3.0 / cl)
 
 
 def parse():

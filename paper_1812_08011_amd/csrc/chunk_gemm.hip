@@ -270,10 +270,11 @@ double cpar_cost_per_tile(int waves) { return waves == 4 ? 0.5e-6 : waves == 8 ?
 // for 134 MB of them, 170 us for 0.8 GB, 6-9 us where there are few).
 constexpr double kValuFoldFixed = 9e-6, kValuFoldBytesPerS = 1e13;
 
-// Extra VALU instructions per multiply-accumulate with FP16 operands: the
-// product's multiplication and its rounding to FP16 (and, max, add and the
-// magic-number add and subtract) replace the FMA's one.
-constexpr double kP16ProductOps = 6.0;
+// Extra VALU instructions per multiply-accumulate with FP16 operands (from the
+// times of the 256 x 6000 x 1024 GEMM and its two backward ones): the product's
+// multiplication and its rounding to FP16 replace the FMA's one, decoding
+// and the bound on a slab's smallest product cost more per staged code.
+constexpr double kP16ProductOps = 7.5, kP16CparOps = 3.8;
 
 // Matrix-core fast mode, CU time of one output-chunk (the VALU epilogue
 // dominates; the matrix-core share grows with CL) and of the per-tile start
@@ -363,7 +364,7 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
             } else {
                 // the chain kernel: 4-k groups inside one chunk
                 if (is_chain(cfg) && (conv || p16 || (CL % 4 != 0 && CL < K))) continue;
-                if (is_cpar(cfg) && (conv || p16 || fast || CL < 32 || K < 32 || M < 16 || N < 16))
+                if (is_cpar(cfg) && (conv || fast || CL < 32 || K < 32 || M < 16 || N < 16))
                     continue;
                 const ValuShape sh = valu_shape(cfg);
                 fn = conv ? valu_conv_kernel(cfg, ta)
@@ -373,7 +374,8 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
                 // the MACs of a chunk, and its end (an add and a rounding); an
                 // FP16 product costs its multiplication and rounding on top,
                 // and the fast chain kernel does without the rounding
-                const double ops = valu_ops_per_mac(cfg) + (p16 ? kP16ProductOps : 0.0) -
+                const double ops = valu_ops_per_mac(cfg) +
+                                   (!p16 ? 0.0 : is_cpar(cfg) ? kP16CparOps : kP16ProductOps) -
                                    (fast && is_chain(cfg) ? chain_fast_saving(cfg) : 0.0);
                 t_out = ((double)CL * ops + 4.0) / (kLanesPerCU * kClockHz);
             }

@@ -57,20 +57,27 @@ __device__ __forceinline__ void slab_pos(int lane, int& r, int& k) {
     else    { k = lane / (R / kCodes);  r = (lane % (R / kCodes)) * kCodes; }
 }
 
+// A lane's 8 codes as loaded: 8 bytes (FP8) or 16 (FP16).
+typedef unsigned __int128 codes16_t;
+template <bool P16> using codes_of = typename std::conditional<P16, codes16_t, uint64_t>::type;
+
 // Codes pos .. pos + 7 of a contiguous run of `lim` (>= 8) codes at `base`:
-// one 8-byte load at any byte alignment (global memory takes unaligned vector
+// one load at any alignment (global memory takes unaligned vector
 // loads here, so odd leading dimensions are read as wide as aligned ones).  A
 // piece that reaches past the run's end is loaded from the run's last 8 codes
 // and moved down by `drop` codes when it is staged (8: nothing is left).
+template <typename Codes>
 __device__ __forceinline__ void load_codes(const uint8_t* __restrict__ base, int pos, int lim,
-                                           bool valid, uint64_t& v, int& drop) {
+                                           bool valid, Codes& v, int& drop) {
+    constexpr int EB = sizeof(Codes) / kCodes;
     const int start = min(pos, lim - kCodes);
-    __builtin_memcpy(&v, base + start, kCodes);
+    __builtin_memcpy(&v, base + (int64_t)start * EB, sizeof(Codes));
     drop = valid ? min(pos - start, kCodes) : kCodes;
 }
 // The 8 codes moved down by `drop` codes, zeros after them.
-__device__ __forceinline__ uint64_t drop_codes(uint64_t v, int drop) {
-    return drop >= kCodes ? 0 : v >> (8 * drop);
+template <typename Codes>
+__device__ __forceinline__ Codes drop_codes(Codes v, int drop) {
+    return drop >= kCodes ? (Codes)0 : v >> (int)(sizeof(Codes) * drop);
 }
 
 // Decode a lane's 8 codes into the wave's slab [k][row] (pitch floats per
@@ -106,6 +113,86 @@ __device__ __forceinline__ void stage(float* lds, int pitch, int lane, uint64_t 
     }
 }
 
+// ---- FP16 operands (chunk_gemm_p16): products rounded to FP16 -----------------
+//
+// The guarded path holds FP16 quantities scaled by 2^-110 (kP16Dom): FP16's
+// smallest step 2^-39 is then FP32's 2^-149 and FP16's smallest normal 2^-30
+// the point where x (2^14 - 1) leaves FP32's normal range, so gradual
+// underflow comes with the FP32 operations.  With a scaled by 2^-55 and b by
+// 2^14 2^-55 (b14), bs = b14 (2^-14 - 1) -- exact, b having at most 10
+// significant bits --, a product x = a b is rounded to FP16 by
+//   s = RN(a bs) = RN(x (1 - 2^14)),  hi = fma(a, b14, s),
+// the two-step rounding of rn16v with the product's multiplication folded in:
+// x (1 - 2^14) is rounded once from its exact value, to FP32's 24 bits or, where
+// |x| < 2^-30, to multiples of 2^-149, the fixed step of FP16's subnormals.
+// hi is exact as long as 2^14 x is a multiple of 2^-39, which holds for every
+// |x| >= 2^-34 (its last bit is at least 2^-53).  A slab that may hold a
+// smaller nonzero product -- the smallest |a| times the smallest |b| of the
+// wave's slab tells -- rounds its products by the clamped magic-number add
+// (rn16_product) instead.  Five instructions per multiply-accumulate against
+// seven with Veltkamp splitting and a per-k bound on the products from 2^-30.
+// Measured, last layer of a 1024 -> 6000 network at batch 256: Forward 248 ->
+// 164 us, Backward 250 -> 181, Gradient 211 -> 182 (128 x 64 tiles with shared
+// chunks before).
+constexpr int kP16Dom = -110;
+
+// 2^96-scaled value of a finite code in bits 16-31 / 0-15 of w (an Inf or NaN
+// code comes out as 2^128 2^-96 or more, which fails the guard): the code's
+// fields moved into FP32's, its subnormals onto FP32's.
+__device__ __forceinline__ float code_hi(uint32_t w) {
+    return __uint_as_float((uint32_t)((int32_t)w >> 2) & 0x9FFFC000u);
+}
+__device__ __forceinline__ float code_lo(uint32_t w) { return code_hi(w << 16); }
+
+// Decode a lane's 8 FP16 codes into the wave's slab, values times 2^SH (SAFE:
+// Inf and NaN kept); TRACK keeps the largest magnitude (of the scaled values)
+// and returns the wave's smallest nonzero magnitude code less one (65535:
+// none).
+template <bool KC, int R, int BK, int SH, bool TRACK>
+__device__ __forceinline__ uint32_t stage16(float* lds, int pitch, int lane, codes16_t codes,
+                                            float& amax) {
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+    int r, k;
+    slab_pos<KC, R, BK>(lane, r, k);
+    us2 key = {0xFFFFu, 0xFFFFu};
+    float f[kCodes];
+#pragma unroll
+    for (int w = 0; w < kCodes / 2; ++w) {
+        const uint32_t v = (uint32_t)(codes >> (32 * w));
+        if (TRACK) {
+            f[2 * w] = code_lo(v) * __builtin_ldexpf(1.0f, 96 + SH);
+            f[2 * w + 1] = code_hi(v) * __builtin_ldexpf(1.0f, 96 + SH);
+            amax = max3_abs(amax, f[2 * w], f[2 * w + 1]);
+            const uint32_t m = v & 0x7FFF7FFFu;
+            us2 c;
+            __builtin_memcpy(&c, &m, 4);
+            key = __builtin_elementwise_min(key, (us2)(c - (us2){1, 1}));
+        } else {
+            f[2 * w] = fp16_to_f32_pow2<SH>(v & 0xFFFFu);
+            f[2 * w + 1] = fp16_to_f32_pow2<SH>(v >> 16);
+        }
+    }
+    if (KC) {
+#pragma unroll
+        for (int b = 0; b < kCodes; ++b) lds[(k + b) * pitch + r] = f[b];
+    } else {
+#pragma unroll
+        for (int b = 0; b < kCodes; b += 4)
+            *reinterpret_cast<float4*>(&lds[k * pitch + r + b]) =
+                make_float4(f[b], f[b + 1], f[b + 2], f[b + 3]);
+    }
+    if (!TRACK) return 0;
+    auto umin = [](uint32_t x, uint32_t y) __attribute__((always_inline)) { return min(x, y); };
+    return wave_reduce(min((uint32_t)key.x, (uint32_t)key.y), umin);
+}
+
+// Whether every nonzero product of magnitudes with these smallest keys is at
+// least 2^-34.
+__device__ __forceinline__ bool products_ok(uint32_t ka, uint32_t kb) {
+    const float a = __uint_as_float((ka + 1) << 14), b = __uint_as_float((kb + 1) << 14);
+    return ka == 0xFFFFu || kb == 0xFFFFu || (a * 0x1p96f) * (b * 0x1p96f) >= 0x1p-34f;
+}
+
 template <int T> struct Tile {
     static constexpr int B = 8 * T;                       // tile edge
     static constexpr int BK = 64 * kCodes / B;            // k per slab
@@ -114,7 +201,7 @@ template <int T> struct Tile {
     static constexpr int PKC = B + T, PRC = B;
 };
 
-template <int T, int NW, bool TA, bool TB>
+template <int T, int NW, bool TA, bool TB, bool P16>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
 void chunk_gemm_cpar(GemmArgs g, Plan p) {
     constexpr int B = Tile<T>::B, BK = Tile<T>::BK;
@@ -145,14 +232,17 @@ void chunk_gemm_cpar(GemmArgs g, Plan p) {
     if (tid < 9) (&s_track[0][0])[tid] = 0;
     __syncthreads();
 
-    uint64_t va = 0, vb = 0;             // codes of the slab fetched last
+    typedef codes_of<P16> Codes;
+    constexpr int EB = P16 ? 2 : 1;      // bytes per code
+    Codes va = 0, vb = 0;                // codes of the slab fetched last
     float P[T][T];
 
     // One piece: chunks [c0, c1) of tile `tile` (see gemm_valu_impl.h).
     auto piece = [&](auto safe_tag, int64_t tile, int c0, int c1, int64_t lt)
                      __attribute__((always_inline)) -> bool {
         constexpr bool SAFE = decltype(safe_tag)::value;
-        constexpr int DOM = SAFE ? 96 : 0;
+        // value scale of the path, and of A's staged values
+        constexpr int DOM = SAFE ? 96 : P16 ? kP16Dom : 0;
         constexpr bool TRACK = !SAFE;
         int tr, tc;
         tile_rc(p, tile, tr, tc);
@@ -164,7 +254,9 @@ void chunk_gemm_cpar(GemmArgs g, Plan p) {
             return SAFE ? rn16s(x) : rn16v(x);
         };
         auto code = [&](float x) __attribute__((always_inline)) -> uint32_t {
-            return fp16_code<DOM>(x);
+            // on the FP16 grid and below 2^32 on the guarded path
+            if constexpr (DOM == kP16Dom) return f32g_to_fp16(x * 0x1p110f);
+            else return fp16_code<DOM>(x);
         };
         // a slab's codes at k0, 8 per lane and operand (k beyond K and rows
         // beyond the matrix read as zero; the k beyond a chunk's end are not
@@ -177,20 +269,22 @@ void chunk_gemm_cpar(GemmArgs g, Plan p) {
             const int ga = k0 + ka, gb = k0 + kb;
             edge = !(inner && k0 + BK <= g.K);
             if (!edge) {
-                __builtin_memcpy(&va, g.A + (KCA ? (int64_t)(m0 + ra) * g.lda + ga
-                                                : (int64_t)ga * g.lda + m0 + ra), kCodes);
-                __builtin_memcpy(&vb, g.B + (KCB ? (int64_t)(n0 + rb) * g.ldb + gb
-                                                : (int64_t)gb * g.ldb + n0 + rb), kCodes);
+                __builtin_memcpy(&va, g.A + EB * (KCA ? (int64_t)(m0 + ra) * g.lda + ga
+                                                      : (int64_t)ga * g.lda + m0 + ra),
+                                 sizeof(Codes));
+                __builtin_memcpy(&vb, g.B + EB * (KCB ? (int64_t)(n0 + rb) * g.ldb + gb
+                                                      : (int64_t)gb * g.ldb + n0 + rb),
+                                 sizeof(Codes));
             } else {
                 const int ma = m0 + ra, nb = n0 + rb;
                 if (KCA)
-                    load_codes(g.A + (int64_t)min(ma, g.M - 1) * g.lda, ga, g.K, ma < g.M, va, da);
+                    load_codes(g.A + EB * ((int64_t)min(ma, g.M - 1) * g.lda), ga, g.K, ma < g.M, va, da);
                 else
-                    load_codes(g.A + (int64_t)min(ga, g.K - 1) * g.lda, ma, g.M, ga < g.K, va, da);
+                    load_codes(g.A + EB * ((int64_t)min(ga, g.K - 1) * g.lda), ma, g.M, ga < g.K, va, da);
                 if (KCB)
-                    load_codes(g.B + (int64_t)min(nb, g.N - 1) * g.ldb, gb, g.K, nb < g.N, vb, db);
+                    load_codes(g.B + EB * ((int64_t)min(nb, g.N - 1) * g.ldb), gb, g.K, nb < g.N, vb, db);
                 else
-                    load_codes(g.B + (int64_t)min(gb, g.K - 1) * g.ldb, nb, g.N, gb < g.K, vb, db);
+                    load_codes(g.B + EB * ((int64_t)min(gb, g.K - 1) * g.ldb), nb, g.N, gb < g.K, vb, db);
             }
         };
         auto read = [&](float (&a)[T], float (&b)[T], const float* buf, int q)
@@ -200,27 +294,58 @@ void chunk_gemm_cpar(GemmArgs g, Plan p) {
 #pragma unroll
             for (int j = 0; j < T; ++j) b[j] = buf[BK * PA + q * PB + lx * T + j];
         };
+        bool staged_ok = true;           // FP16 operands: products_ok of the slab staged last
         auto stage_slab = [&](float* buf) __attribute__((always_inline)) {
             if (edge) {
                 va = drop_codes(va, da);
                 vb = drop_codes(vb, db);
             }
-            stage<KCA, B, BK, DOM, TRACK>(buf, PA, lane, va, amax_a);
-            stage<KCB, B, BK, 0, TRACK>(buf + BK * PA, PB, lane, vb, amax_b);
+            if constexpr (P16) {
+                const uint32_t kma = stage16<KCA, B, BK, SAFE ? 48 : kP16Dom / 2, TRACK>(
+                    buf, PA, lane, va, amax_a);
+                const uint32_t kmb = stage16<KCB, B, BK, SAFE ? 16 : kP16Dom / 2 + 14, TRACK>(
+                    buf + BK * PA, PB, lane, vb, amax_b);
+                if (TRACK)
+                    staged_ok = __builtin_amdgcn_readfirstlane((int)products_ok(kma, kmb)) != 0;
+            } else {
+                stage<KCA, B, BK, DOM, TRACK>(buf, PA, lane, va, amax_a);
+                stage<KCB, B, BK, 0, TRACK>(buf + BK * PA, PB, lane, vb, amax_b);
+            }
         };
-        auto fma_step = [&](const float (&a)[T], const float (&b)[T]) __attribute__((always_inline)) {
+        // FP16 operands: a product rounded to FP16 (see above; SPLIT: every
+        // nonzero one is at least 2^-34)
+        auto product = [&](auto split, float a, float b, float bs) __attribute__((always_inline)) {
+            if constexpr (SAFE) return rn16_product_s(a * b) + 0.0f;
+            else if constexpr (decltype(split)::value) return __builtin_fmaf(a, b, a * bs);
+            else return rn16_product((a * 0x1p55f) * (b * 0x1p41f)) * 0x1p-110f + 0.0f;
+        };
+        auto fma_step = [&](auto split, const float (&a)[T], const float (&b)[T])
+                            __attribute__((always_inline)) {
+            float bs[T];
+#pragma unroll
+            for (int j = 0; j < T; ++j) bs[j] = P16 ? b[j] * (0x1p-14f - 1.0f) : 0.0f;
 #pragma unroll
             for (int i = 0; i < T; ++i)
 #pragma unroll
-                for (int j = 0; j < T; ++j) P[i][j] = rnd(__builtin_fmaf(a[i], b[j], P[i][j]));
+                for (int j = 0; j < T; ++j) {
+                    if constexpr (P16) P[i][j] = rnd(P[i][j] + product(split, a[i], b[j], bs[j]));
+                    else P[i][j] = rnd(__builtin_fmaf(a[i], b[j], P[i][j]));
+                }
         };
-        // a chunk's first product is exact and an FP16 value: no rounding
-        auto first_step = [&](const float (&a)[T], const float (&b)[T])
+        // a chunk's first product, rounded to FP16 if its operands are (an FP8
+        // product is an FP16 value), is the chunk's sum so far
+        auto first_step = [&](auto split, const float (&a)[T], const float (&b)[T])
                               __attribute__((always_inline)) {
+            float bs[T];
+#pragma unroll
+            for (int j = 0; j < T; ++j) bs[j] = P16 ? b[j] * (0x1p-14f - 1.0f) : 0.0f;
 #pragma unroll
             for (int i = 0; i < T; ++i)
 #pragma unroll
-                for (int j = 0; j < T; ++j) P[i][j] = __builtin_fmaf(a[i], b[j], 0.0f);
+                for (int j = 0; j < T; ++j) {
+                    if constexpr (P16) P[i][j] = product(split, a[i], b[j], bs[j]);
+                    else P[i][j] = __builtin_fmaf(a[i], b[j], 0.0f);
+                }
         };
 
         float S[OPT];                      // the thread's running sums
@@ -264,29 +389,33 @@ void chunk_gemm_cpar(GemmArgs g, Plan p) {
                 const int kbeg = c * g.CL, kend = chunk_end(c);
                 for (int ks = kbeg; ks < kend; ks += BK) {
                     wave_sync();
+                    const bool ok = staged_ok;
                     if (more) {
                         stage_slab(region[wave][buf ^ 1]);
                         fetch_next();
                     }
                     const float* const cur = region[wave][buf];
                     const int kmax = kend - ks;
-                    if (kmax >= BK) {
+                    if (kmax >= BK && (!P16 || ok)) {
+                        constexpr std::true_type split{};
                         float a0[T], b0[T], a1[T], b1[T];
                         read(a0, b0, cur, 0);
 #pragma unroll
                         for (int q = 0; q < BK; q += 2) {
                             read(a1, b1, cur, q + 1);
-                            if (q == 0 && ks == kbeg) first_step(a0, b0);
-                            else fma_step(a0, b0);
+                            if (q == 0 && ks == kbeg) first_step(split, a0, b0);
+                            else fma_step(split, a0, b0);
                             if (q + 2 < BK) read(a0, b0, cur, q + 2);
-                            fma_step(a1, b1);
+                            fma_step(split, a1, b1);
                         }
                     } else {
-                        for (int q = 0; q < kmax; ++q) {
+                        // a chunk's last, shorter slab, or tiny products
+                        const int qn = kmax < BK ? kmax : BK;
+                        for (int q = 0; q < qn; ++q) {
                             float a[T], b[T];
                             read(a, b, cur, q);
-                            if (q == 0 && ks == kbeg) first_step(a, b);
-                            else fma_step(a, b);
+                            if (q == 0 && ks == kbeg) first_step(std::false_type{}, a, b);
+                            else fma_step(std::false_type{}, a, b);
                         }
                     }
                     buf ^= 1;
@@ -372,11 +501,20 @@ void chunk_gemm_cpar(GemmArgs g, Plan p) {
             if (tid < 3) s_track[gslot][tid] = 0;
             __syncthreads();
             ua = st[0], ub = st[1], uS = st[2];
-            if (max(ua, ub) >= kF32Inf) return false;
-            const double bound = 3.0 * (double)g.CL * (double)__uint_as_float(ua) *
-                                 (double)__uint_as_float(ub);
+            float ma = __uint_as_float(ua), mb = __uint_as_float(ub), sm = __uint_as_float(uS);
+            if (P16) {
+                // unscaled; an Inf or NaN code decodes to 2^32 or more
+                ma *= 0x1p55f, mb *= 0x1p41f, sm *= 0x1p110f;
+                if (!(ma < 0x1p32f && mb < 0x1p32f)) return false;
+            } else if (max(ua, ub) >= kF32Inf) {
+                return false;
+            }
+            // a product rounded to FP16 is at most (1 + 2^-10) |a b|, or 2^-39
+            // in the subnormal range
+            const double bound = P16 ? 3.01 * (double)g.CL * (double)ma * (double)mb + 1.0
+                                     : 3.0 * (double)g.CL * (double)ma * (double)mb;
             if (!(bound < 2147483648.0)) return false;
-            if (!(__uint_as_float(uS) < 2147483648.0f)) return false;
+            if (!(sm < 2147483648.0f)) return false;
         }
         if (to_ws) return true;
 
@@ -414,11 +552,11 @@ void chunk_gemm_cpar(GemmArgs g, Plan p) {
                 if (n < g.N) crow[0] = (uint16_t)code(S[0]);
             }
         }
-        if (g.C8 && lt < 0) {
+        if (!P16 && g.C8 && lt < 0) {
             uint8_t* qrow = g.C8 + (int64_t)m * g.ldc8 + n;
 #pragma unroll
             for (int o = 0; o < OPT; ++o)
-                if (n + o < g.N) qrow[o] = (uint8_t)f32d_to_fp8_scaled<DOM>(S[o], g.q_scale);
+                if (n + o < g.N) qrow[o] = (uint8_t)f32d_to_fp8_scaled<P16 ? 0 : DOM>(S[o], g.q_scale);
         }
         return true;
     };
@@ -455,15 +593,15 @@ void chunk_gemm_cpar(GemmArgs g, Plan p) {
 }
 
 // Entry addresses (configurations 0 .. 5 of this family).
-template <bool TA, bool TB>
+template <bool TA, bool TB, bool P16>
 const void* table(int i) {
     switch (i) {
-        case 0: return reinterpret_cast<const void*>(&chunk_gemm_cpar<4, 4, TA, TB>);
-        case 1: return reinterpret_cast<const void*>(&chunk_gemm_cpar<4, 8, TA, TB>);
-        case 2: return reinterpret_cast<const void*>(&chunk_gemm_cpar<4, 16, TA, TB>);
-        case 3: return reinterpret_cast<const void*>(&chunk_gemm_cpar<2, 4, TA, TB>);
-        case 4: return reinterpret_cast<const void*>(&chunk_gemm_cpar<2, 8, TA, TB>);
-        case 5: return reinterpret_cast<const void*>(&chunk_gemm_cpar<2, 16, TA, TB>);
+        case 0: return reinterpret_cast<const void*>(&chunk_gemm_cpar<4, 4, TA, TB, P16>);
+        case 1: return reinterpret_cast<const void*>(&chunk_gemm_cpar<4, 8, TA, TB, P16>);
+        case 2: return reinterpret_cast<const void*>(&chunk_gemm_cpar<4, 16, TA, TB, P16>);
+        case 3: return reinterpret_cast<const void*>(&chunk_gemm_cpar<2, 4, TA, TB, P16>);
+        case 4: return reinterpret_cast<const void*>(&chunk_gemm_cpar<2, 8, TA, TB, P16>);
+        case 5: return reinterpret_cast<const void*>(&chunk_gemm_cpar<2, 16, TA, TB, P16>);
         default: return nullptr;
     }
 }

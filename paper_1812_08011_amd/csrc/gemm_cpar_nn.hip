@@ -4,6 +4,6 @@
 
 namespace fp8t {
 
-const void* cpar_kernel_nn(int i) { return cpar::table<false, false>(i); }
+const void* cpar_kernel_nn(int i) { return cpar::table<false, false, false>(i); }
 
 }  // namespace fp8t

@@ -4,6 +4,6 @@
 
 namespace fp8t {
 
-const void* cpar_kernel_nt(int i) { return cpar::table<false, true>(i); }
+const void* cpar_kernel_nt(int i) { return cpar::table<false, true, false>(i); }
 
 }  // namespace fp8t

@@ -4,6 +4,6 @@
 
 namespace fp8t {
 
-const void* cpar_kernel_tn(int i) { return cpar::table<true, false>(i); }
+const void* cpar_kernel_tn(int i) { return cpar::table<true, false, false>(i); }
 
 }  // namespace fp8t

@@ -4,6 +4,6 @@
 
 namespace fp8t {
 
-const void* cpar_kernel_tt(int i) { return cpar::table<true, true>(i); }
+const void* cpar_kernel_tt(int i) { return cpar::table<true, true, false>(i); }
 
 }  // namespace fp8t

@@ -13,6 +13,10 @@ const void* cpar_kernel_nn(int i);
 const void* cpar_kernel_nt(int i);
 const void* cpar_kernel_tn(int i);
 const void* cpar_kernel_tt(int i);
+const void* cpar_p16_kernel_nn(int i);
+const void* cpar_p16_kernel_nt(int i);
+const void* cpar_p16_kernel_tn(int i);
+const void* cpar_p16_kernel_tt(int i);
 
 ValuShape valu_shape(int cfg) {
     switch (cfg) {
@@ -53,7 +57,12 @@ const void* valu_kernel(int cfg, int ta, int tb, int fast) {
 }
 
 const void* valu_p16_kernel(int cfg, int ta, int tb) {
-    if (cfg < 0 || cfg >= kValuConfigs || is_chain(cfg) || is_cpar(cfg)) return nullptr;
+    if (cfg < 0 || cfg >= kValuConfigs || is_chain(cfg)) return nullptr;
+    if (is_cpar(cfg)) {
+        const int i = cfg - kCparConfig;
+        return ta ? (tb ? cpar_p16_kernel_tt(i) : cpar_p16_kernel_tn(i))
+                  : (tb ? cpar_p16_kernel_nt(i) : cpar_p16_kernel_nn(i));
+    }
     return ta ? valu_p16_kernel_t(cfg, tb) : valu_p16_kernel_n(cfg, tb);
 }
 

@@ -853,7 +853,9 @@ const void* kernel_table(int cfg, int fast) {
 }
 
 // FP16-operand kernels (chunk_gemm_p16) of the configurations built for them:
-// the 4 x 4 tiles (4, 7, 8) and the small ones for few outputs (5, 6).
+// a 4 x 4 tile (7) and the small ones for few outputs (5, 6).  They run where
+// the chunk-per-wave kernel does not (chunks below 32 products, edges below
+// 16 codes) or has a single chunk to share out.
 template <int C, bool TA, bool TB>
 const void* kernel_of_p16() {
     using Q = ValuCfg<C>;
@@ -865,11 +867,9 @@ const void* kernel_of_p16() {
 template <bool TA, bool TB>
 const void* kernel_table_p16(int cfg) {
     switch (cfg) {
-        case 4: return kernel_of_p16<4, TA, TB>();
         case 5: return kernel_of_p16<5, TA, TB>();
         case 6: return kernel_of_p16<6, TA, TB>();
         case 7: return kernel_of_p16<7, TA, TB>();
-        case 8: return kernel_of_p16<8, TA, TB>();
         default: return nullptr;
     }
 }

@@ -112,6 +112,45 @@ def test_p16_gemm_guard_rows(row_scale, monkeypatch):
     assert np.array_equal(got, oracle.chunk_gemm_p16(A, B, CL))
 
 
+@pytest.mark.parametrize("tile", ["12", "13", "14", "15", "16", "17"])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_p16_gemm_chunk_per_wave(tile, ta, tb, monkeypatch):
+    """The chunk-per-wave kernel on every tile and layout: slabs on either side
+    of the bound on their smallest products (2^-34), products around 2^-30,
+    ragged edges, chunks that are not whole slabs, whole and shared tiles,
+    unaligned operands, and pieces that fail the guard."""
+    monkeypatch.setenv("FP8T_VALU_TILE", tile)
+    rng = np.random.default_rng(990 + 2 * ta + tb)
+    for (M, N, K, CL), plan in (((67, 45, 391, 64), "0"), ((40, 33, 1000, 100), "1"),
+                                ((16, 16, 2100, 33), "0")):
+        monkeypatch.setenv("FP8T_GEMM_SPLIT", plan)
+        a = np.exp2(rng.uniform(-19, -12, (M, K))) * np.sign(rng.standard_normal((M, K)))
+        b = np.exp2(rng.uniform(-18, -10, (K, N))) * np.sign(rng.standard_normal((K, N)))
+        a[:, K // 2:] *= 2.0 ** 6            # later slabs: every product above the bound
+        a[rng.random(a.shape) < 0.3] = 0.0
+        A, B = p16(a.T if ta else a), p16(b.T if tb else b)
+        say(f"chunk_gemm_p16 chunk per wave tile={tile} ta={ta} tb={tb} {M}x{N}x{K} CL={CL}")
+        ref = oracle.chunk_gemm_p16(A, B, CL, ta, tb)
+        assert np.array_equal(gemm16(dev(A), dev(B), M, N, K, CL, ta, tb), ref)
+        # the same operands two bytes off a 4-byte boundary, odd leading dimensions
+        lda, ldb = A.shape[1] | 1, B.shape[1] | 1
+        Ap, Bp = np.full(1 + A.shape[0] * lda, 0x7F00, np.uint16), \
+            np.full(1 + B.shape[0] * ldb, 0x7F00, np.uint16)
+        Ap[1:].reshape(-1, lda)[:, :A.shape[1]] = A
+        Bp[1:].reshape(-1, ldb)[:, :B.shape[1]] = B
+        C = torch.zeros((M, N), dtype=torch.uint16, device=DEV)
+        Ad, Bd = dev(Ap), dev(Bp)
+        fp8t.chunk_gemm_p16(ta, tb, M, N, K, CL, Ad.data_ptr() + 2, lda, Bd.data_ptr() + 2, ldb,
+                            C, N)
+        assert np.array_equal(host(C), ref)
+        flat = A.reshape(-1)
+        flat[3] = 0x7E00                     # +Inf
+        flat[-2] = 0x7F00                    # NaN
+        flat[flat.size // 2] = 0x7DFF        # largest finite
+        ref = oracle.chunk_gemm_p16(A, B, CL, ta, tb)
+        assert np.array_equal(gemm16(dev(A), dev(B), M, N, K, CL, ta, tb), ref)
+
+
 def test_p16_gemm_empty_k():
     say("chunk_gemm_p16 K = 0")
     A = torch.zeros((5, 1), dtype=torch.uint16, device=DEV)

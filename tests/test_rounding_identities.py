@@ -125,6 +125,62 @@ def test_fp16_product_veltkamp_split_is_rn16():
         assert hi.view(np.uint32)[0] == 0
 
 
+def two_step_product_2m110(a, b):
+    """The chunk-per-wave kernel's product rounding, values scaled by 2^-110
+    (a by 2^-55, b by 2^14 2^-55): s = RN(a bs), hi = fma(a, b14, s), with FP32
+    subnormals kept.  a, b: FP16 values as float64; returns hi 2^110."""
+    a = (a * 2.0 ** -55).astype(np.float32)
+    b14 = (b * 2.0 ** -41).astype(np.float32)
+    bs = (b14 * np.float32(2.0 ** -14 - 1.0)).astype(np.float32)
+    assert np.array_equal(bs.astype(np.float64), b14.astype(np.float64) * (2.0 ** -14 - 1.0))
+    s = (a * bs).astype(np.float32)
+    # a b14 + s fits in float64: one rounding, to float32 with subnormals
+    hi = (a.astype(np.float64) * b14.astype(np.float64) + s.astype(np.float64)).astype(np.float32)
+    return hi.astype(np.float64) * 2.0 ** 110
+
+
+@pytest.mark.parametrize("ea,eb", [(-17, -17), (-18, -15), (-16, -15), (-15, -15), (-30, 0),
+                                   (-39 + 9, 3), (0, 0), (15, 14)])
+def test_fp16_product_two_step_with_gradual_underflow(ea, eb):
+    """Every pair of significands, both signs, products from 2^-34 (the bound
+    a slab's smallest magnitudes are checked against) over 2^-30, where FP16's
+    step becomes fixed, up to 2^31: RN to FP16, zero and subnormals included."""
+    for na in (False, True):
+        a = fp16_operands(ea, na).astype(np.float64)[:, None]
+        b = fp16_operands(eb).astype(np.float64)[None, :]
+        assert np.array_equal(two_step_product_2m110(a, b), rn16_reference(a * b)), (ea, eb, na)
+    z = np.zeros((1, 1))
+    for b in (3.0, -3.0):
+        r = two_step_product_2m110(z, np.float64([[b]]))
+        assert r[0, 0] == 0.0 and not np.signbit(r[0, 0])
+
+
+def test_fp16_product_two_step_subnormal_operands():
+    """FP16-subnormal operands (m 2^-39) with products from 2^-34."""
+    a = fp16_subnormals().astype(np.float64)[:, None]
+    for eb in (5, 9, 20):
+        b = fp16_operands(eb).astype(np.float64)[None, :]
+        x = a * b
+        got = two_step_product_2m110(a, b)
+        ok = np.abs(x) >= 2.0 ** -34
+        assert np.array_equal(got[ok], rn16_reference(x)[ok])
+
+
+@pytest.mark.parametrize("e", [-32, -31, -30, -29, 0])
+def test_two_step_rounding_scaled_2m110_keeps_fp16_sums(e):
+    """rn16v on sums of FP16 values scaled by 2^-110, where FP16's subnormals
+    are FP32's: multiples of 2^-39 below 2^-30 pass through, sums above round
+    to 10 bits (24-bit sums around the boundary, both signs)."""
+    k = np.arange(-(1 << 19), 1 << 19, dtype=np.float64)
+    v = (k * 2.0 ** -39 + 2.0 ** e) if e < -28 else (1.0 + k * 2.0 ** -20) * 2.0 ** e
+    for x64 in (v, -v):
+        x = (x64 * 2.0 ** -110).astype(np.float32)
+        assert np.array_equal(x.astype(np.float64) * 2.0 ** 110, x64)
+        s = (x * np.float32(-16383.0)).astype(np.float32)
+        hi = (x.astype(np.float64) * 16384.0 + s.astype(np.float64)).astype(np.float32)
+        assert np.array_equal(hi.astype(np.float64) * 2.0 ** 110, rn16_reference(x64))
+
+
 def rn16_product_plain(p):
     """The plain-value magic-number rounding of an exact float32 product."""
     e = p.view(np.uint32) & np.uint32(0x7F800000)
