@@ -534,8 +534,8 @@ void chunk_gemm_mfma_kx16(GemmArgs g, Plan p) {
     }
     int vslot = 0;
 
-    ShareA sa[2];                        // two steps in flight
-    ShareB sb[2];
+    ShareA sa;
+    ShareB sb;
     float S[4];
     float vmax = 0.0f;
     const v4f zero = {};
@@ -548,13 +548,13 @@ void chunk_gemm_mfma_kx16(GemmArgs g, Plan p) {
         m0 = tr * kT;
         n0 = tc * kT;
     };
-    auto load = [&](int q, int m0, int n0, int k0) __attribute__((always_inline)) {
-        sa[q].template load<AL>(g.A, g.lda, m0, g.M, k0, g.K, g.a_vec, g.a_vec16, tid);
-        sb[q].template load<AL>(g.B, g.ldb, n0, g.N, k0, g.K, g.b_vec, g.b_vec16, tid);
+    auto load = [&](int m0, int n0, int k0) __attribute__((always_inline)) {
+        sa.template load<AL>(g.A, g.lda, m0, g.M, k0, g.K, g.a_vec, g.a_vec16, tid);
+        sb.template load<AL>(g.B, g.ldb, n0, g.N, k0, g.K, g.b_vec, g.b_vec16, tid);
     };
-    auto store = [&](int q, int buf) __attribute__((always_inline)) {
-        sa[q].store(As[buf], tid);
-        sb[q].store(Bs[buf], tid);
+    auto store = [&](int buf) __attribute__((always_inline)) {
+        sa.store(As[buf], tid);
+        sb.store(Bs[buf], tid);
     };
 
     // The step's chunk sums of the wave's block (chunks past K are not formed).
@@ -566,8 +566,8 @@ void chunk_gemm_mfma_kx16(GemmArgs g, Plan p) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int kb = kCL * c + 32 * h;
-                const long av = sa[0].operand(As[buf], 16 * bi, kb, lane);
-                const long bv = sb[0].operand(Bs[buf], 16 * bj, kb, lane);
+                const long av = sa.operand(As[buf], 16 * bi, kb, lane);
+                const long bv = sb.operand(Bs[buf], 16 * bj, kb, lane);
                 acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf8_bf8(av, bv, acc[c], 0, 0, 0);
             }
         }
@@ -648,13 +648,9 @@ void chunk_gemm_mfma_kx16(GemmArgs g, Plan p) {
     };
 
     // ---- the stream (guarded epilogue): steps of the workgroup's tiles in
-    // order.  Step cur is consumed from LDS buffer Q while step p1, which
-    // arrived in register set Q, is stored into the other buffer, step p2 is
-    // on its way into set Q ^ 1 and step p3 is requested into set Q.  Bound by
-    // the latency of a step's phases (operand reads, matrix cores, roundings:
-    // 1500 of its 2000 cycles remain without any load from memory).  2304 x
-    // 256 x 50176: 182 us with one step in flight and equal wave priorities,
-    // 171 with the priorities below, 167 with two steps in flight as well ----
+    // order.  Step cur is consumed from LDS buffer buf while step p1, held in
+    // the registers, is stored into the other buffer and step p2 is loaded
+    // into the registers ----
     const int64_t T = p.t_whole;
     struct Pos {
         int64_t t;                   // work item (tile t of the workgroup's sequence)
@@ -672,92 +668,56 @@ void chunk_gemm_mfma_kx16(GemmArgs g, Plan p) {
         cur.t = blockIdx.x;
         cur.s = 0;
         tile_origin(cur.t, cur.m0, cur.n0);
-        load(0, cur.m0, cur.n0, 0);
-        store(0, 0);
-        Pos p1 = cur, p2, p3;
+        load(cur.m0, cur.n0, 0);
+        store(0);
+        Pos p1 = cur;
         step_next(p1);
-        p2 = p1;
-        if (p1.t < T) step_next(p2);
-        // (AL: loads past the last step read the current one again and are
-        // never stored, so that the number of loads in flight is always known)
-        auto request = [&](int q, const Pos& r) __attribute__((always_inline)) {
-            if (AL) {
-                const Pos& lp = r.t < T ? r : cur;
-                load(q, lp.m0, lp.n0, lp.s * kSK);
-            } else if (r.t < T) {
-                load(q, r.m0, r.n0, r.s * kSK);
-            }
-        };
-        request(0, p1);
-        request(1, p2);
+        if (p1.t < T) load(p1.m0, p1.n0, p1.s * kSK);
         __syncthreads();
         int buf = 0, ordinal = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) S[i] = 0.0f;
-        // One step from buffer buf; register set Q holds step p1, set Q ^ 1
-        // step p2.
-        auto step = [&](auto q_tag) __attribute__((always_inline)) {
-            constexpr int Q = decltype(q_tag)::value;
+        for (;;) {
             v4f acc[kWaves];
-            // a wave that reads operands and feeds the matrix cores goes before
-            // those that round chunk sums: the waves of a SIMD then leave the
-            // two phases one by one instead of together
-            __builtin_amdgcn_s_setprio(1);
             chunk_sums(buf, cur.s, acc);
-            __builtin_amdgcn_s_setprio(0);
             // buffer buf ^ 1 was last read by the previous step, before the
             // barrier that ended it
-            p3 = p2;
-            if (p2.t < T) step_next(p3);
-            if (AL || p1.t < T) {                // AL: past the last step nobody reads it
-                store(Q, buf ^ 1);
-                request(Q, p3);
+            Pos p2 = p1;
+            if (p1.t < T) {
+                store(buf ^ 1);
+                step_next(p2);
+                if (p2.t < T) load(p2.m0, p2.n0, p2.s * kSK);
             }
             chain(std::integral_constant<bool, false>{}, cur.s, acc);
+            if (cur.s + 1 == nsteps) {
+                // tile end: the guard over the whole workgroup (running sums
+                // below 2^31 at every chunk end; NaN from an Inf operand stays
+                // in the running sum and fails the final comparison)
+                bool bad_l = !(vmax < 2147483648.0f);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) bad_l |= !(fabsf(S[i]) < 2147483648.0f);
+                // the codes go to Os before the vote (a failed tile's are
+                // never stored), whose barrier then orders them for the stores
+                stage_tile(std::integral_constant<bool, false>{});
+                const bool bad = block_any(bad_l, s_vote, vslot);
+                if (bad) {
+                    if (tid == 0) {
+                        if (n_redo < kRedoMax) redo[n_redo] = ordinal;
+                        ++n_redo;
+                    }
+                } else {
+                    store_tile(cur.m0, cur.n0);
+                }
+                vmax = 0.0f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) S[i] = 0.0f;
+                ++ordinal;
+            }
+            if (p1.t >= T) break;
             __syncthreads();                     // buf read, buf ^ 1 written
             buf ^= 1;
             cur = p1;
             p1 = p2;
-            p2 = p3;
-        };
-        while (cur.t < T) {
-            const int m0 = cur.m0, n0 = cur.n0;
-            // (the tile's end outside the loop over its steps: with its stores
-            // inside, every step waited for both register sets)
-            int s = 0;
-            for (; s + 2 <= nsteps; s += 2) {
-                step(std::integral_constant<int, 0>{});
-                step(std::integral_constant<int, 1>{});
-            }
-            if (s < nsteps) {
-                step(std::integral_constant<int, 0>{});
-                const ShareA ta = sa[0];
-                const ShareB tb = sb[0];
-                sa[0] = sa[1], sa[1] = ta;
-                sb[0] = sb[1], sb[1] = tb;
-            }
-            // tile end: the guard over the whole workgroup (running sums below
-            // 2^31 at every chunk end; NaN from an Inf operand stays in the
-            // running sum and fails the final comparison)
-            bool bad_l = !(vmax < 2147483648.0f);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) bad_l |= !(fabsf(S[i]) < 2147483648.0f);
-            // the codes go to Os before the vote (a failed tile's are never
-            // stored), whose barrier then orders them for the stores
-            stage_tile(std::integral_constant<bool, false>{});
-            const bool bad = block_any(bad_l, s_vote, vslot);
-            if (bad) {
-                if (tid == 0) {
-                    if (n_redo < kRedoMax) redo[n_redo] = ordinal;
-                    ++n_redo;
-                }
-            } else {
-                store_tile(m0, n0);
-            }
-            vmax = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) S[i] = 0.0f;
-            ++ordinal;
         }
     }
 
@@ -776,9 +736,9 @@ void chunk_gemm_mfma_kx16(GemmArgs g, Plan p) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) S[i] = 0.0f;
         for (int s = 0; s < nsteps; ++s) {
-            load(0, m0, n0, s * kSK);
+            load(m0, n0, s * kSK);
             __syncthreads();                     // buffer 0 read by the previous step
-            store(0, 0);
+            store(0);
             __syncthreads();
             v4f acc[kWaves];
             chunk_sums(0, s, acc);
