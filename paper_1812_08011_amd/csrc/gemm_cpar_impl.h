@@ -390,9 +390,14 @@ void chunk_gemm_cpar(GemmArgs g, Plan p) {
                 for (int ks = kbeg; ks < kend; ks += BK) {
                     wave_sync();
                     const bool ok = staged_ok;
+                    // a wave that stages goes before those that compute, so
+                    // that it has its next slab under way while they do
+                    // (1000 x 777 x 3001: 165 -> 160 us)
                     if (more) {
+                        __builtin_amdgcn_s_setprio(1);
                         stage_slab(region[wave][buf ^ 1]);
                         fetch_next();
+                        __builtin_amdgcn_s_setprio(0);
                     }
                     const float* const cur = region[wave][buf];
                     const int kmax = kend - ks;
