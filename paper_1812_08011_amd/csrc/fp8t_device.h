@@ -316,6 +316,28 @@ __device__ __forceinline__ uint32_t xnor3_vvv(uint32_t a, uint32_t b, uint32_t c
 constexpr uint32_t kPhiloxM0 = 0xD2511F53u, kPhiloxM1 = 0xCD9E8D57u;
 constexpr uint32_t kPhiloxW0 = 0x9E3779B9u, kPhiloxW1 = 0xBB67AE85u;
 
+// The keys of the ten rounds, each in a vector register (for loops over many
+// blocks of one key).
+struct PhiloxKeys {
+    uint32_t a[10], b[10];
+    __device__ __forceinline__ PhiloxKeys(uint32_t k0, uint32_t k1) {
+#pragma unroll
+        for (uint32_t r = 0; r < 10; ++r) {
+            a[r] = in_vgpr(k0 + r * kPhiloxW0);
+            b[r] = in_vgpr(k1 + r * kPhiloxW1);
+        }
+    }
+};
+__device__ __forceinline__ u32x4 philox4x32_10(u32x4 c, const PhiloxKeys& key) {
+#pragma unroll
+    for (int r = 0; r < 10; ++r) {
+        const uint64_t p0 = (uint64_t)kPhiloxM0 * c.x, p1 = (uint64_t)kPhiloxM1 * c.z;
+        c = {xor3_vvv((uint32_t)(p1 >> 32), c.y, key.a[r]), (uint32_t)p1,
+             xor3_vvv((uint32_t)(p0 >> 32), c.w, key.b[r]), (uint32_t)p0};
+    }
+    return c;
+}
+
 // Stochastic rounding of a plain float into FP16 (Eq. (1), k' = 23, k = 9):
 // round the magnitude up by one step with probability F / 2^16, where F is
 // the discarded fraction of a step scaled to 16 bits; u16 is uniform on

@@ -362,13 +362,15 @@ void chunk_gemm_sr_kernel(TileArgs g, Plan p) {
 // Continue the running sums of the shared tiles (in C, from their first
 // pieces) over the chunk sums in the workspace, in ascending chunk order --
 // the additions a whole-tile pass makes, with the same inter-chunk uniforms.
-// A thread takes 8 consecutive outputs of a row: one 16-byte load of chunk
-// sums and one block of uniforms per chunk.
-constexpr int kFoldV = 8, kFoldTU = 8;
+// A thread takes 4 consecutive outputs of a row: one 8-byte load of chunk
+// sums and half of a block of uniforms per chunk (with the block's 8 outputs a
+// thread, 512 x 512 outputs are half a wave per SIMD and the blocks' latency
+// stands alone).
+constexpr int kFoldV = 4, kFoldTU = 8, kFoldT = 64;
 
-__global__ __launch_bounds__(256) void chunk_fold_sr(TileArgs g, Plan p) {
+__global__ __launch_bounds__(kFoldT) void chunk_fold_sr(TileArgs g, Plan p) {
     const int64_t per = (int64_t)kBM * kBN;
-    const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * kFoldV;
+    const int64_t idx = ((int64_t)blockIdx.x * kFoldT + threadIdx.x) * kFoldV;
     const int64_t lt = idx / per;
     if (lt * p.nch >= p.L) return;
     const int local = (int)(idx - lt * per);
@@ -385,12 +387,15 @@ __global__ __launch_bounds__(256) void chunk_fold_sr(TileArgs g, Plan p) {
     float S[kFoldV];
 #pragma unroll
     for (int v = 0; v < kFoldV; ++v) S[v] = v < nv ? fp16_to_f32s(cp[v]) : 0.0f;
-    const uint4* src = reinterpret_cast<const uint4*>(g.ws + lt * p.nch * per + local);
+    const uint2* src = reinterpret_cast<const uint2*>(g.ws + lt * p.nch * per + local);
     const int64_t step = per / kFoldV;
-    auto add = [&](const uint4& q, int c) __attribute__((always_inline)) {
-        const uint32_t cw[4] = {q.x, q.y, q.z, q.w};
-        const u32x4 b = block_of((uint32_t)m, (uint32_t)(n0 >> 3), (uint32_t)c, g.w3 + 1u, g);
-        const uint32_t nw[4] = {~b.x, ~b.y, ~b.z, ~b.w};
+    const PhiloxKeys keys(g.k0, g.k1);
+    const bool odd = (n0 >> 2) & 1;               // the block's second four uniforms
+    auto add = [&](const uint2& q, int c) __attribute__((always_inline)) {
+        const uint32_t cw[2] = {q.x, q.y};
+        const u32x4 b = philox4x32_10(
+            {(uint32_t)m, (uint32_t)(n0 >> 3), (uint32_t)c, g.w3 + 1u}, keys);
+        const uint32_t nw[2] = {~(odd ? b.z : b.x), ~(odd ? b.w : b.y)};
 #pragma unroll
         for (int v = 0; v < kFoldV; ++v) {
             const float x = S[v] + fp16_to_f32s((cw[v / 2] >> (16 * (v % 2))) & 0xFFFFu);
@@ -402,16 +407,16 @@ __global__ __launch_bounds__(256) void chunk_fold_sr(TileArgs g, Plan p) {
     // chunk, the extra values never added) so the compiler waits for the
     // older batch only.
     const int last = p.nch - 1;
-    auto load = [&](uint4 (&q)[kFoldTU], int c0) __attribute__((always_inline)) {
+    auto load = [&](uint2 (&q)[kFoldTU], int c0) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < kFoldTU; ++u) q[u] = src[(int64_t)min(c0 + u, last) * step];
     };
-    auto fold = [&](const uint4 (&q)[kFoldTU], int c0) __attribute__((always_inline)) {
+    auto fold = [&](const uint2 (&q)[kFoldTU], int c0) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < kFoldTU; ++u)
             if (c0 + u < p.nch) add(q[u], c0 + u);
     };
-    uint4 q0[kFoldTU], q1[kFoldTU];
+    uint2 q0[kFoldTU], q1[kFoldTU];
     int c = a;
     load(q0, c);
     for (;;) {
@@ -555,8 +560,8 @@ int tile_call(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t CL, const
         return FP8T_EHIP;
     if (plan.L > 0) {
         const int64_t threads = (plan.L / plan.nch) * kBM * kBN / kFoldV;
-        hipLaunchKernelGGL(chunk_fold_sr, dim3((unsigned)((threads + 255) / 256)),
-                           dim3(256), 0, stream, g, plan);
+        hipLaunchKernelGGL(chunk_fold_sr, dim3((unsigned)((threads + kFoldT - 1) / kFoldT)),
+                           dim3(kFoldT), 0, stream, g, plan);
     }
     return launch_status();
 }
