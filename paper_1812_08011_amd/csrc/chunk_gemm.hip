@@ -495,7 +495,34 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
     return best;
 }
 
+// The short-K variant of the wave-independent kernel: one tile per workgroup, K
+// whole 64-k slabs that fit LDS at once.  64-row tiles where they make at least
+// four rounds of resident workgroups (three of 48 KB per CU): with fewer, the
+// last round is too empty a share of the call (3136 x 4608 x 256, 1764 tiles:
+// 13.7 us with 32 rows against 14.5; 50176 x 576 x 64, 3920 tiles: 14.9
+// against 14.0; both kernels' figures at gemm_mfma_short.hip).
+bool short_k(const Choice& ch, const GemmArgs& g) {
+    return ch.fn == mfma_wave_kernel(0) && ch.plan.G == ch.plan.t_whole && g.K % 64 == 0 &&
+           g.K <= 256;
+}
+int launch_short(const Choice& ch, GemmArgs g, hipStream_t stream) {
+    Plan p = ch.plan;
+    const int64_t t64 = p.tiles_n * (((int64_t)g.M + 63) / 64);
+    const int rb = t64 >= 12 * (int64_t)device_cus() ? 2 : 1;
+    if (rb == 2) {
+        p.t_whole = t64;
+        p.G = (int)t64;
+        p.xcd_remap = t64 % 8 == 0;
+    }
+    void* args[] = {&g, &p};
+    if (hipLaunchKernel(mfma_short_kernel(rb, g.K / 64, g.CL == 64), dim3(p.G), dim3(ch.NT), args,
+                        0, stream) != hipSuccess)
+        return FP8T_EHIP;
+    return launch_status();
+}
+
 int launch_plan(const Choice& ch, GemmArgs g, hipStream_t stream) {
+    if (short_k(ch, g)) return launch_short(ch, g, stream);
     void* args[] = {&g, const_cast<Plan*>(&ch.plan)};
     const void* fn = ch.fn_aligned && mfma_kx_aligned(g) ? ch.fn_aligned : ch.fn;
     if (hipLaunchKernel(fn, dim3(ch.plan.G), dim3(ch.NT), args, 0, stream) != hipSuccess)

@@ -64,6 +64,10 @@ const void* mfma_kx16_kernel_aligned(int ta, int tb);
 // launch_transpose_bytes makes), leading dimensions below 2^26; nullptr for
 // trans_a = 1.
 const void* mfma_wave_kernel(int ta);
+// Its variant for K = 64 ns, ns 1 .. 4 (gemm_mfma_short.hip): 32 rb x 128 tiles
+// (rb 1 or 2), one per workgroup, same operand conditions; one: CL = 64 (each
+// slab a chunk).
+const void* mfma_short_kernel(int rb, int ns, int one);
 // Bt[n * ldt + k] = B[k * ldb + n] for k < K, n < N, on `stream` (Bt 16-byte
 // aligned, ldt a multiple of 16).
 void launch_transpose_bytes(const uint8_t* B, int64_t ldb, int K, int N, uint8_t* Bt, int64_t ldt,
