@@ -14,7 +14,13 @@
 // * chunk_gemm_mfma_kx, chunk_gemm_mfma_kx16 (gemm_mfma_kx.hip) -- the fast
 //   mode for CL = 64 on GEMMs with few outputs and a long K: a 64 x 64 tile
 //   per 16-wave workgroup, a step's chunks spread over the waves, or (kx16,
-//   the one the planner picks) a 16 x 16 block per wave over the whole K.
+//   the one the planner picks) a 16 x 16 block per wave over the whole K;
+// * chunk_gemm_mfma_wave (gemm_mfma_wave.hip) -- the fast mode for CL a
+//   multiple of 64, every wave streaming its own block, and its variant for K
+//   up to 256, chunk_gemm_mfma_short (gemm_mfma_short.hip);
+// * chunk_gemm_chain (gemm_chain.hip) and chunk_gemm_cpar (gemm_cpar_impl.h) --
+//   the exact mode for few outputs: one tile's chain per workgroup, or a chunk
+//   per wave.
 #include <type_traits>
 
 #include "fp8t_device.h"
