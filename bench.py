@@ -46,19 +46,20 @@ FP8_MFMA_MAC_S = 5.0e15 / 2                             # dense FP8 5.0 PFLOP/s
 # HBM traffic of the exact-mode chunk_gemm calls of one step, from two
 # rocprofv3 counter passes (FETCH_SIZE, WRITE_SIZE) over this benchmark,
 # calibrated by the counters of a plain device copy of known size (fetch x2.0,
-# write x1.0); average calibrated bytes per call (forward 189.9 MB,
-# backward-data 300.0 MB, weight-gradient 2402.6 MB including the chunk sums
+# write x1.0); average calibrated bytes per call (forward 190.2 MB,
+# backward-data 293.9 MB, weight-gradient 547.4 MB including the chunk sums
 # of its shared tiles and the fold pass).  Valid only for the kernel sources
 # they were measured on (EXACT_KERNEL_SOURCES): any change to them reports null.
-TRAFFIC_SOURCES_SHA256 = "db50901dabab05030d5d7fa646f332cc0669e2180f3c2ded13dbd31be5b5c982"
-EXACT_TRAFFIC_BYTES_PER_CALL = 963.8e6
+TRAFFIC_SOURCES_SHA256 = "4dc6d8852e35dced7cb4e441e5b27a6295d2749a09e4a6bf8087a7f8e0c49030"
+EXACT_TRAFFIC_BYTES_PER_CALL = 343.8e6
 
 
 # The sources that decide what an exact-mode chunk_gemm call runs: the VALU
 # kernel, its instantiations, the planner and fold pass, the shared device code.
 EXACT_KERNEL_SOURCES = ("chunk_gemm.hip", "fp8t_device.h", "fp8t_host.h", "gemm_plan.h",
                         "gemm_chain.hip", "gemm_cpar_impl.h", "gemm_cpar_nn.hip",
-                        "gemm_cpar_nt.hip", "gemm_cpar_tn.hip", "gemm_cpar_tt.hip", "gemm_valu.h", "gemm_valu.hip", "gemm_valu_impl.h",
+                        "gemm_cpar_nt.hip", "gemm_cpar_tn.hip", "gemm_cpar_tt.hip",
+                        "gemm_valu.h", "gemm_valu.hip", "gemm_valu_impl.h",
                         "gemm_valu_nn.hip", "gemm_valu_nt.hip", "gemm_valu_tn.hip",
                         "gemm_valu_tt.hip")
 
