@@ -190,8 +190,8 @@ __device__ __forceinline__ void stage_fast(const uint8_t* __restrict__ p, int64_
 
 // One launch of the persistent plan: workgroup w takes whole tiles w, w + G,
 // ..., then its range of the shared tile-chunks.
-template <bool TA, bool TB>
-__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4)))
+template <bool TA, bool TB, int WPE>
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(WPE)))
 void chunk_gemm_sr_kernel(TileArgs g, Plan p) {
     const uint8_t* __restrict__ A = g.A;
     const uint8_t* __restrict__ B = g.B;
@@ -259,11 +259,13 @@ void chunk_gemm_sr_kernel(TileArgs g, Plan p) {
             const int hi = sb + kBK < kend ? sb + kBK : kend;
             __syncthreads();               // the previous slab is consumed
             // stage op(A)[m0.., lo..hi) and op(B)[lo..hi), n0..) as floats;
-            // rows, columns and k outside are zero
+            // rows, columns and k outside are zero (two codes at a time: with
+            // all eight in flight four waves per SIMD spilled up to 96
+            // registers, 832 x 3488 x 16: 29.9 us against 21.4)
             if (lo == sb && hi == sb + kBK && m0 + kBM <= g.M && g.a_vec) {
                 stage_fast<true, !TA>(A, g.lda, m0, sb, As, tid);
             } else {
-#pragma unroll
+#pragma unroll 2
                 for (int q = 0; q < kBM * kBK / kNT; ++q) {
                     const int e = tid + kNT * q;
                     int mm, kk;
@@ -278,7 +280,7 @@ void chunk_gemm_sr_kernel(TileArgs g, Plan p) {
             if (lo == sb && hi == sb + kBK && n0 + kBN <= g.N && g.b_vec) {
                 stage_fast<false, TB>(B, g.ldb, n0, sb, Bs, tid);
             } else {
-#pragma unroll
+#pragma unroll 2
                 for (int q = 0; q < kBN * kBK / kNT; ++q) {
                     const int e = tid + kNT * q;
                     int nn, kk;
@@ -447,59 +449,96 @@ __global__ void fill_zero16(uint16_t* __restrict__ C, int64_t ldc, int M, int N)
         C[(i / N) * ldc + i % N] = 0;
 }
 
+template <int WPE>
 const void* tile_kernel(int ta, int tb) {
-    if (!ta && !tb) return reinterpret_cast<const void*>(&chunk_gemm_sr_kernel<false, false>);
-    if (!ta && tb) return reinterpret_cast<const void*>(&chunk_gemm_sr_kernel<false, true>);
-    if (ta && !tb) return reinterpret_cast<const void*>(&chunk_gemm_sr_kernel<true, false>);
-    return reinterpret_cast<const void*>(&chunk_gemm_sr_kernel<true, true>);
+    if (!ta && !tb) return reinterpret_cast<const void*>(&chunk_gemm_sr_kernel<false, false, WPE>);
+    if (!ta && tb) return reinterpret_cast<const void*>(&chunk_gemm_sr_kernel<false, true, WPE>);
+    if (ta && !tb) return reinterpret_cast<const void*>(&chunk_gemm_sr_kernel<true, false, WPE>);
+    return reinterpret_cast<const void*>(&chunk_gemm_sr_kernel<true, true, WPE>);
 }
 
 struct TilePlan {
-    Plan plan;
+    Plan plan{};
     size_t ws_bytes = 0;
     bool ok = false;
 };
 
-// One workgroup per resident slot; with a workspace allowed, tiles that do
-// not divide evenly over the slots have their chunks shared out (every
-// workgroup then ends with the same number of chunks).
+// Time of a plan's parts in microseconds, fitted to calls of 1 .. 2060 tiles, K
+// 16 .. 16000 and CL 1 .. 500, as whole tiles and shared out over two and four
+// workgroups per CU (8% root mean square): one k of a tile with r workgroups on
+// its CU, a chunk's end, and the fold pass (launch, each chunk of an output's
+// chain, and a million chunk sums).
+constexpr double kTileUsPerK[5] = {0.0, 0.365, 0.51, 0.72, 0.895};
+constexpr double kTileUsPerChunk = 0.23;
+constexpr double kTileFoldUs = 7.0, kTileFoldUsPerChunk = 0.36, kTileFoldUsPerMillion = 0.52;
+
+// r workgroups per CU, each `chunks` chunks of CL (one after the other)
+double tile_us(int64_t r, double chunks, int64_t CL) {
+    if (r > 4) r = 4;
+    return chunks * ((double)CL * kTileUsPerK[r] + (double)r * kTileUsPerChunk);
+}
+
+// Whole tiles, or (with a workspace allowed) the chunks of the tiles that do
+// not divide evenly over the slots shared out, every workgroup then ending
+// with the same number of chunks: over four workgroups per CU, or over two,
+// the kernel's two register budgets.  Four resident waves per SIMD round about
+// 10% more products a second than two (1000 tiles of K 512: 503 us against 553),
+// but a call of few chunks loses more to the fold pass and to workgroups with a
+// chunk each (K 65, CL 64: 512 tiles whole 43 us, shared over four 80; 468 tiles
+// 44 / 79, over two 57), hence the estimate.
 TilePlan plan_tile(const void* fn, int64_t M, int64_t N, int64_t K, int64_t CL, bool allow_ws) {
     TilePlan r;
     const int cus = device_cus();
-    const int occ = kernel_occupancy(fn, kNT);
+    int occ = kernel_occupancy(fn, kNT);
     if (cus <= 0 || occ <= 0) return r;
-    int64_t gmax = (int64_t)cus * occ;
+    if (occ > 4) occ = 4;
     const int force_g = env_int("FP8T_GEMM_WGS", 0);
-    if (force_g > 0 && force_g < gmax) gmax = force_g;
     const int force_split = env_int("FP8T_GEMM_SPLIT", -1);
     const int64_t tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN;
     const int64_t T = tiles_m * tiles_n;
     const int64_t nch = (K + CL - 1) / CL;
-    Plan p{};
+    auto slots = [&](int per_cu) {
+        const int64_t g = (int64_t)cus * per_cu;
+        return force_g > 0 && force_g < g ? (int64_t)force_g : g;
+    };
+    Plan& p = r.plan;
     p.tiles_n = tiles_n;
     p.nch = (int)nch;
-    const int64_t G = T < gmax ? T : gmax;
-    const int64_t q = T / gmax;
-    // the plain plan leaves T % gmax tiles for a last, partly idle round
-    const bool split = allow_ws && force_split != 0 && T % gmax != 0 &&
-                       (force_split == 1 || q < 4) && nch > 1;
-    if (!split) {
-        p.G = (int)G;
-        p.t_whole = T;
-        p.L = 0;
-    } else {
-        int64_t Gs = gmax;
-        if (Gs > T * nch) Gs = T * nch;
-        p.G = (int)Gs;
-        p.t_whole = (T / Gs) * Gs;
-        p.L = (T - p.t_whole) * nch;
-        r.ws_bytes = (size_t)(T - p.t_whole) * nch * kBM * kBN * sizeof(uint16_t) + kWsAlign;
+    p.t_whole = T;
+    p.L = 0;
+    p.G = (int)(T < slots(occ) ? T : slots(occ));
+    // rounds of `occ` tiles per CU, then the rest
+    const int64_t per_cu = (T + cus - 1) / cus;
+    const double tile_chunks = (double)K / (double)CL;
+    double est = (double)(per_cu / occ) * tile_us(occ, tile_chunks, CL) +
+                 (per_cu % occ ? tile_us(per_cu % occ, tile_chunks, CL) : 0.0);
+    for (int wgs : {occ, 2}) {
+        const int64_t g = slots(wgs), q = T / g;
+        // with many rounds the last, partly idle one costs little
+        if (!allow_ws || force_split == 0 || nch == 1 || T % g == 0 ||
+            (q >= 4 && force_split != 1))
+            continue;
+        Plan c{};
+        c.tiles_n = tiles_n;
+        c.nch = (int)nch;
+        c.G = (int)(g < T * nch ? g : T * nch);
+        c.t_whole = (T / c.G) * c.G;
+        c.L = (T - c.t_whole) * nch;
+        if (c.L == 0) continue;
+        const double sums = (double)c.L * kBM * kBN;
+        const double e = tile_us((c.G + cus - 1) / cus,
+                                 (double)(T / c.G) * tile_chunks + (double)((c.L + c.G - 1) / c.G),
+                                 CL) + kTileFoldUs + kTileFoldUsPerChunk * (double)nch +
+                         kTileFoldUsPerMillion * sums * 1e-6;
+        if (e >= est && !(force_split == 1 && p.L == 0)) continue;
+        est = e;
+        p = c;
+        r.ws_bytes = (size_t)c.L * kBM * kBN * sizeof(uint16_t) + kWsAlign;
     }
     p.xcd_remap = p.t_whole % 8 == 0 && p.G % 8 == 0;
     if (env_int("FP8T_GEMM_VERBOSE", 0))
-        fprintf(stderr, "[fp8t tile plan] occ %d G %d T %lld t_whole %lld L %lld ws %zu\n", occ,
-                p.G, (long long)T, (long long)p.t_whole, (long long)p.L, r.ws_bytes);
-    r.plan = p;
+        fprintf(stderr, "[fp8t tile plan] occ %d G %d T %lld t_whole %lld L %lld ws %zu est %.1f us\n",
+                occ, p.G, (long long)T, (long long)p.t_whole, (long long)p.L, r.ws_bytes, est);
     r.ok = true;
     return r;
 }
@@ -530,7 +569,7 @@ int tile_call(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t CL, const
         return launch_status();
     }
     if (CL > K) CL = K;
-    const void* fn = tile_kernel(ta, tb);
+    const void* fn = tile_kernel<4>(ta, tb);
     const TilePlan tp = plan_tile(fn, M, N, K, CL, workspace_bytes > 0);
     if (!tp.ok) return FP8T_EHIP;
     if (tp.ws_bytes > workspace_bytes) return FP8T_EWORKSPACE;
@@ -555,6 +594,11 @@ int tile_call(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t CL, const
     g.a_vec = aligned(A, 8) && lda % 8 == 0;
     g.b_vec = aligned(B, 8) && ldb % 8 == 0;
     Plan plan = tp.plan;
+    // two workgroups per CU or fewer: the registers of four waves per SIMD are
+    // not needed, and with twice as many nothing is spilled and the blocks of a
+    // thread's rows overlap more (93 x 2043 x 2781: 1270 -> 1105 us; 16 x 16 x
+    // 16: 13.4 -> 11.4)
+    if (plan.G <= 2 * device_cus()) fn = tile_kernel<2>(ta, tb);
     void* args[] = {&g, &plan};
     if (hipLaunchKernel(fn, dim3(plan.G), dim3(kNT), args, 0, stream) != hipSuccess)
         return FP8T_EHIP;
@@ -569,7 +613,7 @@ int tile_call(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t CL, const
 size_t tile_workspace(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t CL) {
     if (!tile_args_ok(ta, tb, M, N, K, CL)) return 0;
     if (M == 0 || N == 0 || K == 0) return 0;
-    const TilePlan tp = plan_tile(tile_kernel(ta, tb), M, N, K, CL > K ? K : CL, true);
+    const TilePlan tp = plan_tile(tile_kernel<4>(ta, tb), M, N, K, CL > K ? K : CL, true);
     return tp.ok ? tp.ws_bytes : 0;
 }
 

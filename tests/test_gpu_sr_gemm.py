@@ -135,3 +135,23 @@ def test_sr_gemm_key_schedule_extremes(seed, offset, CL):
     say(f"chunk_gemm_sr keys seed={seed} offset={offset} CL={CL}")
     got = sr_gemm(dev(A), dev(B), M, N, K, CL, 0, 0, seed, offset)
     assert np.array_equal(got, oracle.chunk_gemm_sr(A, B, CL, seed=seed, offset=offset))
+
+
+@pytest.mark.parametrize("M,N,K,CL", [(2048, 1024, 65, 64), (2048, 1024, 64, 1), (1872, 1024, 65, 64)])
+def test_sr_gemm_few_chunks_stay_whole(M, N, K, CL):
+    """Tiles that fill two workgroups per CU (or nearly) and have few chunks
+    are not shared out (43 us whole against 80 for the first)."""
+    say(f"chunk_gemm_sr plan {M}x{N}x{K} CL={CL}")
+    assert fp8t.chunk_gemm_sr_workspace_size(0, 0, M, N, K, CL) == 0
+
+
+@pytest.mark.parametrize("M,N", [(70, 70), (1100, 2000)])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_sr_gemm_both_register_budgets(ta, tb, M, N):
+    """At most two workgroups per CU, and more than two (576 tiles on 256 CUs),
+    run on different register budgets: the same bits."""
+    K, CL = 37, 16
+    A, B = operands(np.random.default_rng(79), M, N, K, ta, tb, scale=4.0)
+    say(f"chunk_gemm_sr register budgets {M}x{N} ta={ta} tb={tb}")
+    got = sr_gemm(dev(A), dev(B), M, N, K, CL, ta, tb, 17, 3, use_ws=False)
+    assert np.array_equal(got, oracle.chunk_gemm_sr(A, B, CL, ta, tb, seed=17, offset=3))
