@@ -298,27 +298,38 @@ void chunk_gemm_sr_kernel(TileArgs g, Plan p) {
             // kernel at two waves per SIMD)
             for (int kseg = lo; kseg < hi;) {
                 const int kstop = cend < hi ? (int)cend : hi;
+                auto product = [&](int k, auto round) __attribute__((always_inline)) {
+                    const float4 a4 = *reinterpret_cast<const float4*>(&As[k - sb][ty * kT]);
+                    const float4 b4 = *reinterpret_cast<const float4*>(&Bs[k - sb][tx * kT]);
+                    const float av[4] = {a4.x, a4.y, a4.z, a4.w};
+                    const float bv[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+                    for (int r = 0; r < kT; ++r)
+#pragma unroll
+                        for (int c = 0; c < kT; ++c)
+                            P[r][c] = round(__builtin_fmaf(av[r], bv[c], P[r][c]), r, c);
+                };
+                // A chunk's first product goes into +0: an FP16 value, which no
+                // uniform changes.  On an odd k, or as the whole chunk, it is
+                // taken without blocks, so that a pair of k cut by a chunk's end
+                // draws them once (otherwise twice: 203 x 1065 x 2674, CL 1,
+                // 3089 us against 2065).
+                if (kseg == (int64_t)chunk * g.CL && ((kseg & 1) || kstop == kseg + 1)) {
+                    product(kseg, [](float x, int, int) __attribute__((always_inline)) { return x; });
+                    ++kseg;
+                }
 #pragma unroll 1
-                for (int gq = kseg & ~1; gq < kstop; gq += 2) {
-                    // rows' blocks for k = gq, gq + 1 (complemented words)
+                for (int gq = kseg; gq < kstop; gq += 2) {
+                    // rows' blocks for k = gq (even), gq + 1 (complemented words)
                     uint32_t nw[kT][4];
                     bits.blocks((uint32_t)(gq >> 1), keys, g, nw);
-                    auto product = [&](auto half) __attribute__((always_inline)) {
-                        constexpr int s = decltype(half)::value;
-                        const int k = gq + s;
-                        const float4 a4 = *reinterpret_cast<const float4*>(&As[k - sb][ty * kT]);
-                        const float4 b4 = *reinterpret_cast<const float4*>(&Bs[k - sb][tx * kT]);
-                        const float av[4] = {a4.x, a4.y, a4.z, a4.w};
-                        const float bv[4] = {b4.x, b4.y, b4.z, b4.w};
-#pragma unroll
-                        for (int r = 0; r < kT; ++r)
-#pragma unroll
-                            for (int c = 0; c < kT; ++c)
-                                P[r][c] = sr16s(__builtin_fmaf(av[r], bv[c], P[r][c]),
-                                                sr_addend(nw[r][2 * s + c / 2], c % 2));
-                    };
-                    if (gq >= kseg) product(std::integral_constant<int, 0>{});
-                    if (gq + 1 < kstop) product(std::integral_constant<int, 1>{});
+                    product(gq, [&](float x, int r, int c) __attribute__((always_inline)) {
+                        return sr16s(x, sr_addend(nw[r][c / 2], c % 2));
+                    });
+                    if (gq + 1 < kstop)
+                        product(gq + 1, [&](float x, int r, int c) __attribute__((always_inline)) {
+                            return sr16s(x, sr_addend(nw[r][2 + c / 2], c % 2));
+                        });
                 }
                 kseg = kstop;
                 if (kstop == cend) chunk_end();

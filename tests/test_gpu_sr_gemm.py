@@ -155,3 +155,25 @@ def test_sr_gemm_both_register_budgets(ta, tb, M, N):
     say(f"chunk_gemm_sr register budgets {M}x{N} ta={ta} tb={tb}")
     got = sr_gemm(dev(A), dev(B), M, N, K, CL, ta, tb, 17, 3, use_ws=False)
     assert np.array_equal(got, oracle.chunk_gemm_sr(A, B, CL, ta, tb, seed=17, offset=3))
+
+
+@pytest.mark.parametrize("plan", ["whole", "shared"])
+@pytest.mark.parametrize("CL", [1, 2, 3, 7])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_sr_gemm_chunk_starts(ta, tb, CL, plan, monkeypatch):
+    """Chunks that start on an odd k or are a single product: their first
+    product takes no random bits (it is an FP16 value already), with zeros,
+    -0, subnormal products, Inf and NaN among the first products."""
+    if plan == "shared":
+        monkeypatch.setenv("FP8T_GEMM_SPLIT", "1")
+        monkeypatch.setenv("FP8T_GEMM_WGS", "3")
+    M, N, K = 70, 66, 75
+    A, B = operands(np.random.default_rng(78), M, N, K, ta, tb, scale=4.0)
+    rows, cols = (A.T if ta else A), (B if not tb else B.T)
+    rows[2, :] = 0x01                        # 2^-16: products down to 2^-32
+    cols[:, 3] = 0x81
+    rows[5, ::3] = 0x80                      # -0
+    rows[7, 7], rows[8, 21], rows[9, 1] = 0x7C, 0x7F, 0xFC
+    say(f"chunk_gemm_sr chunk starts plan={plan} CL={CL} ta={ta} tb={tb}")
+    got = sr_gemm(dev(A), dev(B), M, N, K, CL, ta, tb, 91, 5)
+    assert np.array_equal(got, oracle.chunk_gemm_sr(A, B, CL, ta, tb, seed=91, offset=5))
