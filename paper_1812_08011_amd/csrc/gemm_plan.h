@@ -22,21 +22,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-namespace fp8t {
+#include "gemm_conv_words.h"
 
-// Implicit lowering of a convolution (Sec. 2.2: a convolution is computed by
-// lowering its input and then a GEMM): the lowered matrix Xcol, M = N * OH *
-// OW rows (output pixels, row-major n, oh, ow) by KH * KW * C columns (order
-// kh, kw, c), is read straight from the NHWC input X:
-//   Xcol(p, (kh, kw, c)) = X[n, oh * stride - pad + kh, ow * stride - pad + kw, c]
-// (0 outside the image).
-struct ConvGeom {
-    int H, W, C;        // input height, width, channels
-    int KW, KWC;        // kernel width, KW * C
-    int OW, OHW;        // output width, OH * OW
-    int pad, stride;
-    int vec;            // C % 4 == 0 and X 4-byte aligned: 4 channels per load
-};
+namespace fp8t {
 
 struct GemmArgs {
     const uint8_t* A;

@@ -41,8 +41,10 @@ const void* valu_p16_kernel(int cfg, int ta, int tb);
 
 // Exact-mode kernel of configuration cfg whose A operand is an implicitly
 // lowered convolution input (GemmArgs::conv); trans_b = 0; null where not
-// built (only configuration 4).
-const void* valu_conv_kernel(int cfg, int ta);
+// built (all but configurations 4 and 7).  walk: input positions carried from
+// slab to slab (ConvGeom::vec, and with trans_a = 0 every piece starting at a
+// multiple of 4 k) instead of divided out per word.
+const void* valu_conv_kernel(int cfg, int ta, int walk);
 
 // chunk_gemm_chain with 2 x 2 (shape 0), 1 x 2 (1) or 1 x 1 (2) outputs per
 // lane for the given operand layouts and mode (fast: sum a chunk in FP32 and

@@ -7,21 +7,21 @@
 namespace fp8t {
 namespace {
 
-template <int C>
+template <int C, int CONV>
 const void* conv_kernel_of(int ta) {
     using Q = valu_impl::ValuCfg<C>;
     if (!ta)
         return reinterpret_cast<const void*>(&valu_impl::chunk_gemm_valu<
-            Q::TM, Q::TN, Q::LM, Q::LN, Q::BK, Q::PF, Q::WPE, false, false, false, true>);
+            Q::TM, Q::TN, Q::LM, Q::LN, Q::BK, Q::PF, Q::WPE, false, false, false, CONV>);
     return reinterpret_cast<const void*>(&valu_impl::chunk_gemm_valu<
-        Q::TM, Q::TN, Q::LM, Q::LN, Q::BK, Q::PF, Q::WPE, true, false, false, true>);
+        Q::TM, Q::TN, Q::LM, Q::LN, Q::BK, Q::PF, Q::WPE, true, false, false, CONV>);
 }
 
 }  // namespace
 
-const void* valu_conv_kernel(int cfg, int ta) {
-    if (cfg == 4) return conv_kernel_of<4>(ta);
-    if (cfg == 7) return conv_kernel_of<7>(ta);
+const void* valu_conv_kernel(int cfg, int ta, int walk) {
+    if (cfg == 4) return walk ? conv_kernel_of<4, 2>(ta) : conv_kernel_of<4, 1>(ta);
+    if (cfg == 7) return walk ? conv_kernel_of<7, 2>(ta) : conv_kernel_of<7, 1>(ta);
     return nullptr;
 }
 

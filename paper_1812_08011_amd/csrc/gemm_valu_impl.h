@@ -40,6 +40,7 @@
 #pragma once
 
 #include "fp8t_device.h"
+#include "gemm_conv_words.h"
 #include "gemm_valu.h"
 
 namespace fp8t {
@@ -87,133 +88,6 @@ __device__ __forceinline__ void slab_load(const uint8_t* __restrict__ ptr, int64
         reg[w] = v;
     }
 }
-
-// The same for an implicitly lowered convolution input (ConvGeom): the
-// operand is Xcol (KC: element (r, k) = Xcol(r, k), rows are output pixels)
-// or Xcol^T (element (r, k) = Xcol(k, r)).  A word holds 4 consecutive Xcol
-// columns of one pixel: 4 consecutive channels of one input position when
-// C % 4 == 0 (one 4-byte load), otherwise gathered byte by byte.
-__device__ __forceinline__ uint32_t xcol_byte(const uint8_t* __restrict__ X, const ConvGeom& cg,
-                                              int pix, int col) {
-    const int n = pix / cg.OHW, rem = pix - n * cg.OHW;
-    const int oh = rem / cg.OW, ow = rem - oh * cg.OW;
-    const int kh = col / cg.KWC, r2 = col - kh * cg.KWC;
-    const int kw = r2 / cg.C, c = r2 - kw * cg.C;
-    const int ih = oh * cg.stride - cg.pad + kh, iw = ow * cg.stride - cg.pad + kw;
-    if ((unsigned)ih >= (unsigned)cg.H || (unsigned)iw >= (unsigned)cg.W) return 0u;
-    return X[(((int64_t)n * cg.H + ih) * cg.W + iw) * cg.C + c];
-}
-
-template <bool KC, int R, int BK, int NT, int W>
-__device__ __forceinline__ void slab_load_conv(const uint8_t* __restrict__ X, const ConvGeom& cg,
-                                               int r0, int rows, int k0, int kend, int tid,
-                                               uint32_t (&reg)[W]) {
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-        const int d = tid + NT * w;
-        int r, k;
-        if (KC) { r = d / (BK / 4); k = (d % (BK / 4)) * 4; }
-        else    { k = d / (R / 4);  r = (d % (R / 4)) * 4; }
-        const int gr = r0 + r, gk = k0 + k;
-        // pixel and first column of the word; valid columns [col, col + nb)
-        const int pix = KC ? gr : gk, col = KC ? gk : gr;
-        const bool in = gr < rows && gk < kend;
-        const int lim = KC ? kend - gk : rows - gr;
-        const int nb = lim < 4 ? lim : 4;
-        uint32_t v = 0;
-        if (in) {
-            // one 4-byte load when the word is 4 aligned channels of one input
-            // position (chunk ranges need not start at a multiple of 4)
-            if (cg.vec && (col & 3) == 0) {
-                const int n = pix / cg.OHW, rem = pix - n * cg.OHW;
-                const int oh = rem / cg.OW, ow = rem - oh * cg.OW;
-                const int kh = col / cg.KWC, r2 = col - kh * cg.KWC;
-                const int kw = r2 / cg.C, c = r2 - kw * cg.C;
-                const int ih = oh * cg.stride - cg.pad + kh, iw = ow * cg.stride - cg.pad + kw;
-                if ((unsigned)ih < (unsigned)cg.H && (unsigned)iw < (unsigned)cg.W)
-                    v = *reinterpret_cast<const uint32_t*>(
-                        X + (((int64_t)n * cg.H + ih) * cg.W + iw) * cg.C + c);
-                if (nb < 4) v &= (1u << (8 * nb)) - 1u;
-            } else {
-                for (int b = 0; b < nb; ++b) v |= xcol_byte(X, cg, pix, col + b) << (8 * b);
-            }
-        }
-        reg[w] = v;
-    }
-}
-
-// The same walk with the index arithmetic carried along, for words of 4 aligned
-// channels (ConvGeom::vec, first k a multiple of 4): a piece's slabs follow
-// each other in k, so each thread keeps its words' positions in the input and
-// its column's (kh, kw, c) and advances them by BK instead of dividing the
-// pixel and column of every word (8 divisions per slab and thread; Forward and
-// Gradient kernels of a 32 x 14 x 14 x 256 -> 256 3 x 3 convolution 243 / 240
-// -> 233 / 234 us).
-template <bool KC, int R, int BK, int NT, int W>
-struct ConvWalk {
-    static_assert(KC ? NT % (BK / 4) == 0 : NT % (R / 4) == 0, "a thread's words share a column");
-    int kh, kw, c;              // the thread's column: KC that of the next slab, else fixed
-    int n[W], y[W], x[W];       // KC: image and input origin of the word's pixel (a row of
-                                // the operand); else its pixel (n, oh, ow) of the next slab
-    __device__ __forceinline__ void start(const ConvGeom& cg, int r0, int k0, int tid) {
-        const int col = KC ? k0 + (tid % (BK / 4)) * 4 : r0 + (tid % (R / 4)) * 4;
-        kh = col / cg.KWC;
-        const int r2 = col - kh * cg.KWC;
-        kw = r2 / cg.C;
-        c = r2 - kw * cg.C;
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-            const int d = tid + NT * w;
-            const int pix = KC ? r0 + d / (BK / 4) : k0 + d / (R / 4);
-            n[w] = pix / cg.OHW;
-            const int rem = pix - n[w] * cg.OHW;
-            const int oh = rem / cg.OW, ow = rem - oh * cg.OW;
-            y[w] = KC ? oh * cg.stride - cg.pad : oh;
-            x[w] = KC ? ow * cg.stride - cg.pad : ow;
-        }
-    }
-    // the slab at k0 (the walk stands there), then on to k0 + BK
-    __device__ __forceinline__ void load(const uint8_t* __restrict__ X, const ConvGeom& cg, int r0,
-                                         int rows, int k0, int kend, int tid, uint32_t (&reg)[W]) {
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-            const int d = tid + NT * w;
-            const int gr = r0 + (KC ? d / (BK / 4) : (d % (R / 4)) * 4);
-            const int gk = k0 + (KC ? (d % (BK / 4)) * 4 : d / (R / 4));
-            const int ih = (KC ? y[w] : y[w] * cg.stride - cg.pad) + kh;
-            const int iw = (KC ? x[w] : x[w] * cg.stride - cg.pad) + kw;
-            uint32_t v = 0;
-            if (gr < rows && gk < kend && (unsigned)ih < (unsigned)cg.H &&
-                (unsigned)iw < (unsigned)cg.W) {
-                v = *reinterpret_cast<const uint32_t*>(
-                    X + (((int64_t)n[w] * cg.H + ih) * cg.W + iw) * cg.C + c);
-                const int lim = KC ? kend - gk : rows - gr;
-                if (lim < 4) v &= (1u << (8 * lim)) - 1u;
-            }
-            reg[w] = v;
-        }
-        if (KC) {
-            c += BK;
-            while (c >= cg.C) {
-                c -= cg.C;
-                if (++kw == cg.KW) { kw = 0; ++kh; }
-            }
-        } else {
-            // BK pixels on: whole images, rows and columns, with carries
-            const int OH = cg.OHW / cg.OW;
-            const int dn = BK / cg.OHW, dr = BK - dn * cg.OHW;
-            const int dy = dr / cg.OW, dx = dr - dy * cg.OW;
-#pragma unroll
-            for (int w = 0; w < W; ++w) {
-                x[w] += dx;
-                y[w] += dy;
-                if (x[w] >= cg.OW) { x[w] -= cg.OW; ++y[w]; }
-                n[w] += dn;
-                if (y[w] >= OH) { y[w] -= OH; ++n[w]; }
-            }
-        }
-    }
-};
 
 // Decode a thread's words into the LDS slab, laid out [k][row] with `pitch`
 // floats per k, each value times 2^SH.  The FP8 codes are the OCP E5M2
@@ -401,10 +275,11 @@ __device__ __forceinline__ void slab_store16(float* lds, int pitch, int tid,
     }
 }
 
-// CONV: the A operand is the implicit lowering of an NHWC input (g.conv).
+// CONV: the A operand is the implicit lowering of an NHWC input (g.conv), its
+// words' positions divided out (1) or carried along (2: ConvWalk).
 // P16: A and B hold FP16 codes (chunk_gemm_p16, exact mode only).
 template <int TM, int TN, int LM, int LN, int BK, bool PF, int WPE, bool TA, bool TB, bool FAST,
-          bool CONV = false, bool P16 = false>
+          int CONV = 0, bool P16 = false>
 __global__ __launch_bounds__(LM * LN) __attribute__((amdgpu_waves_per_eu(WPE)))
 void chunk_gemm_valu(GemmArgs g, Plan p) {
     constexpr int NT = LM * LN;
@@ -453,19 +328,15 @@ void chunk_gemm_valu(GemmArgs g, Plan p) {
         __syncthreads();
     }
 
-    // CONV: the incremental walk over the lowered input (uniform: taken or not)
-    typename std::conditional<CONV, ConvWalk<KCA, BM, BK, NT, WA>, int>::type walk;
-    bool walking = false;
+    typename std::conditional<CONV == 2, ConvWalk<KCA, BM, BK, NT, WA>, int>::type walk;
     auto load_a = [&](int m0, int k0, int kend) __attribute__((always_inline)) {
         if constexpr (P16)
             slab_load16<KCA, BM, BK, NT, WA>(reinterpret_cast<const uint16_t*>(g.A), g.lda,
                                              g.a_vec, m0, g.M, k0, kend, tid, ra);
-        else if constexpr (CONV) {
-            if (walking)
-                walk.load(g.A, g.conv, m0, g.M, k0, kend, tid, ra);
-            else
-                slab_load_conv<KCA, BM, BK, NT, WA>(g.A, g.conv, m0, g.M, k0, kend, tid, ra);
-        }
+        else if constexpr (CONV == 2)
+            walk.load(g.A, g.conv, m0, g.M, k0, kend, tid, ra);
+        else if constexpr (CONV == 1)
+            slab_load_conv<KCA, BM, BK, NT, WA>(g.A, g.conv, m0, g.M, k0, kend, tid, ra);
         else
             slab_load<KCA, BM, BK, NT, WA>(g.A, g.lda, g.a_vec, m0, g.M, k0, kend, tid, ra);
     };
@@ -666,10 +537,7 @@ void chunk_gemm_valu(GemmArgs g, Plan p) {
             }
             return __all(ok);
         };
-        if constexpr (CONV) {
-            walking = g.conv.vec && (!KCA || (kbeg & 3) == 0);
-            if (walking) walk.start(g.conv, m0, kbeg, tid);
-        }
+        if constexpr (CONV == 2) walk.start(g.conv, m0, kbeg, tid);
         fetch_slab(kbeg);
         stage_slab(0);
         __syncthreads();

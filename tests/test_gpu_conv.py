@@ -72,6 +72,32 @@ def test_conv_fwd_and_wgrad_match_oracle(plan, monkeypatch):
         assert np.array_equal(got, oconv.conv2d_wgrad(X8, D8, KH, KW, pad, stride, CL)), geom
 
 
+@pytest.mark.parametrize("plan", ["4", "7", "4-shared", "7-shared"])
+@pytest.mark.parametrize("C,KH,KW,pad,stride", [(4, 3, 3, 1, 1), (12, 3, 3, 1, 2), (16, 1, 1, 0, 1),
+                                               (20, 5, 5, 2, 2), (36, 3, 2, 0, 3)])
+def test_conv_carried_positions(C, KH, KW, pad, stride, plan, monkeypatch):
+    """Input positions carried from slab to slab (32 k): channels below half a
+    slab, up to a slab and above it, sums of several slabs in both directions,
+    and chunk lengths on either side of the Gradient's rule."""
+    monkeypatch.setenv("FP8T_VALU_TILE", plan[0])
+    if plan.endswith("shared"):
+        monkeypatch.setenv("FP8T_GEMM_SPLIT", "1")
+        monkeypatch.setenv("FP8T_GEMM_WGS", "5")
+    rng = np.random.default_rng(1015)
+    N, H, W, Cout = 3, 13, 11, 21
+    geom = (N, H, W, C, KH, KW, pad, stride)
+    OH, OW = oconv.out_size(H, W, KH, KW, pad, stride)
+    X8 = oracle.fp8_quantize(np.maximum(rng.standard_normal((N, H, W, C)), 0).astype(np.float32))
+    W8 = oracle.fp8_quantize((rng.standard_normal((KH * KW * C, Cout)) * 0.3).astype(np.float32))
+    D8 = oracle.fp8_quantize(rng.standard_normal((N * OH * OW, Cout)).astype(np.float32))
+    for CL in (8, 30, 64, 128):
+        say(f"conv2d carried positions plan={plan} geom={geom} CL={CL}")
+        got = run_conv("fwd", dev(X8), dev(W8), geom, Cout, CL)
+        assert np.array_equal(got, oconv.conv2d_fwd(X8, W8, KH, KW, pad, stride, CL)), CL
+        got = run_conv("wgrad", dev(X8), dev(D8), geom, Cout, CL)
+        assert np.array_equal(got, oconv.conv2d_wgrad(X8, D8, KH, KW, pad, stride, CL)), CL
+
+
 def test_conv_misaligned_input_takes_byte_loads():
     rng = np.random.default_rng(1011)
     N, H, W, C, KH, KW, pad, stride, Cout, CL = 2, 6, 6, 8, 3, 3, 1, 1, 16, 64
