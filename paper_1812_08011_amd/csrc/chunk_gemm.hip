@@ -335,7 +335,7 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
                  bool allow_ws, bool conv = false, size_t ws_cap = SIZE_MAX,
                  bool wave_ok = true) {
     Choice best;
-    const int cus = device_cus();
+    const int cus = device_cus(), dev = current_device();
     if (cus <= 0) return best;
     const bool mf = kind == MFMA_FAST;
     const bool p16 = kind == VALU_P16;
@@ -389,7 +389,7 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
             const bool cpar = !mf && is_cpar(cfg);
             const int nw = cpar ? cpar_waves(cfg) : 1;
             if (cpar) t_tile = cpar_cost_per_tile(nw);
-            int occ = kernel_occupancy(fn, NT);
+            int occ = kernel_occupancy(fn, NT, dev);
             if (occ <= 0) continue;
             if (occ > 8) occ = 8;
             const int64_t tiles_m = (M + BM - 1) / BM;

@@ -500,7 +500,7 @@ double tile_us(int64_t r, double chunks, int64_t CL) {
 TilePlan plan_tile(const void* fn, int64_t M, int64_t N, int64_t K, int64_t CL, bool allow_ws) {
     TilePlan r;
     const int cus = device_cus();
-    int occ = kernel_occupancy(fn, kNT);
+    int occ = kernel_occupancy(fn, kNT, current_device());
     if (cus <= 0 || occ <= 0) return r;
     if (occ > 4) occ = 4;
     const int force_g = env_int("FP8T_GEMM_WGS", 0);
