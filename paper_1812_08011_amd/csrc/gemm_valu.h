@@ -36,7 +36,7 @@ ValuShape valu_shape(int cfg);
 const void* valu_kernel(int cfg, int ta, int tb, int fast);
 
 // Kernel of configuration cfg with FP16 operands (chunk_gemm_p16: products
-// rounded to FP16, exact mode); null where not built (configurations 0-4, 8).
+// rounded to FP16, exact mode); null where not built (configurations 0-3).
 const void* valu_p16_kernel(int cfg, int ta, int tb);
 
 // Exact-mode kernel of configuration cfg whose A operand is an implicitly

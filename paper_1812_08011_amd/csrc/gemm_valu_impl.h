@@ -582,11 +582,21 @@ void chunk_gemm_valu(GemmArgs g, Plan p) {
                     }
                 } else {
                     const bool fresh = crem == g.CL;
-                    for (int q = kk; q < kk + seg; ++q) {
+                    auto one = [&](int q) __attribute__((always_inline)) {
                         float a[TM], b[TN];
                         lds_read(a, b, buf, q);
                         if (q == kk && fresh) first_step(vsplit, a, b);
                         else fma_step(vsplit, a, b);
+                    };
+                    if constexpr (P16) {
+                        // not unrolled: three roundings of a product (and four
+                        // k of each) spilled up to 157 registers, 110 now
+                        // (2048 x 2048 x 2048, CL 2048, 128 x 64 tiles: 1191
+                        // -> 1015 us)
+#pragma clang loop unroll(disable)
+                        for (int q = kk; q < kk + seg; ++q) one(q);
+                    } else {
+                        for (int q = kk; q < kk + seg; ++q) one(q);
                     }
                 }
                 kk += seg;
@@ -811,23 +821,29 @@ const void* kernel_table(int cfg, int fast) {
 }
 
 // FP16-operand kernels (chunk_gemm_p16) of the configurations built for them:
-// a 4 x 4 tile (7) and the small ones for few outputs (5, 6).  They run where
-// the chunk-per-wave kernel does not (chunks below 32 products, edges below
-// 16 codes) or has a single chunk to share out.
+// the 4 x 4 tiles (4, 7, 8) and the small ones for few outputs (5, 6).  They run
+// where the chunk-per-wave kernel does not (chunks below 32 products, edges
+// below 16 codes) or has few chunks to share out.  The 64 x 64 tile is given
+// the registers of three waves per SIMD: FP16 operands' staging and product
+// roundings spilled up to 176 with four (45545 x 395 x 15, trans_a: 111 us with
+// four, 82 with three; 256 x 6000 x 1024, CL 16: 304 / 288), and the larger
+// tiles, which run longer sums, were slower with three.
 template <int C, bool TA, bool TB>
 const void* kernel_of_p16() {
     using Q = ValuCfg<C>;
     return reinterpret_cast<const void*>(&chunk_gemm_valu<Q::TM, Q::TN, Q::LM, Q::LN, Q::BK,
-                                                          Q::PF, Q::WPE, TA, TB, false, false,
-                                                          true>);
+                                                          Q::PF, C == 4 ? 3 : Q::WPE, TA, TB,
+                                                          false, 0, true>);
 }
 
 template <bool TA, bool TB>
 const void* kernel_table_p16(int cfg) {
     switch (cfg) {
+        case 4: return kernel_of_p16<4, TA, TB>();
         case 5: return kernel_of_p16<5, TA, TB>();
         case 6: return kernel_of_p16<6, TA, TB>();
         case 7: return kernel_of_p16<7, TA, TB>();
+        case 8: return kernel_of_p16<8, TA, TB>();
         default: return nullptr;
     }
 }

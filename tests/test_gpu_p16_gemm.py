@@ -112,6 +112,74 @@ def test_p16_gemm_guard_rows(row_scale, monkeypatch):
     assert np.array_equal(got, oracle.chunk_gemm_p16(A, B, CL))
 
 
+def ran(capfd, tile):
+    """The configuration the last call ran on (FP8T_GEMM_VERBOSE=1)."""
+    err = capfd.readouterr().err
+    chosen = [l for l in err.splitlines() if "] chose kind 3 " in l]
+    assert chosen and chosen[-1].split("cfg ")[1].split()[0] == tile, chosen[-1:]
+
+
+@pytest.mark.parametrize("guard", ["1", "0"])
+@pytest.mark.parametrize("tile", ["4", "5", "6", "7", "8"])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_p16_gemm_register_tiles(tile, ta, tb, guard, monkeypatch, capfd):
+    """The register tiles (chunks below 32 products, edges below 16, and what
+    the planner prefers them for), each forced: subnormal and overflowing
+    products, Inf and NaN; products mostly below 2^-30; slabs on either side
+    of the bound that picks the product's rounding; chunks of one slab, of
+    parts of one and of several."""
+    monkeypatch.setenv("FP8T_VALU_TILE", tile)
+    monkeypatch.setenv("FP8T_GEMM_GUARD", guard)
+    monkeypatch.setenv("FP8T_GEMM_VERBOSE", "1")
+    rng = np.random.default_rng(991 + 2 * ta + tb)
+
+    def check(a, b, CL, what, plant=False):
+        A, B = p16(a.T if ta else a), p16(b.T if tb else b)
+        if plant:
+            rows = A.T if ta else A
+            rows[3, 5] = 0x7E00               # +Inf
+            rows[4, 6] = 0x7F00               # NaN
+            rows[5, :] = 0x0001               # smallest subnormal
+            rows[6, :] = 0x7DFF               # largest finite
+        (M, K), N = a.shape, b.shape[1]
+        say(f"chunk_gemm_p16 {what} tile={tile} guard={guard} ta={ta} tb={tb} {M}x{N}x{K} CL={CL}")
+        got = gemm16(dev(A), dev(B), M, N, K, CL, ta, tb)
+        ran(capfd, tile)
+        ref = oracle.chunk_gemm_p16(A, B, CL, ta, tb)
+        assert np.array_equal(got, ref), (what, CL, np.argwhere(got != ref)[:5])
+
+    def signed(shape, lo, hi):
+        return np.exp2(rng.uniform(lo, hi, shape)) * np.sign(rng.standard_normal(shape))
+
+    for M, N, K, CL in ((70, 40, 256, 7), (70, 40, 150, 16), (11, 37, 200, 64)):
+        check(signed((M, K), -39, 31), signed((K, N), -20, 5), CL, "ranges", plant=True)
+        check(signed((M, K), -39, -5), signed((K, N), -20, 0), CL, "small magnitudes")
+        a, b = signed((M, K), -18, -11), signed((K, N), -16, -8)
+        a[:, K // 2:] *= 2.0 ** 8             # later slabs: every product above 2^-30
+        a[rng.random(a.shape) < 0.3] = 0.0
+        check(a, b, CL, "mixed slabs")
+
+
+@pytest.mark.parametrize("tile", ["4", "5", "6", "7", "8"])
+@pytest.mark.parametrize("row_scale", [2.0 ** -28, 2.0 ** 17])
+def test_p16_gemm_register_tiles_guard_rows(tile, row_scale, monkeypatch, capfd):
+    """test_p16_gemm_guard_rows on each register tile: shared tiles some of
+    whose pieces fail the guard."""
+    monkeypatch.setenv("FP8T_VALU_TILE", tile)
+    monkeypatch.setenv("FP8T_GEMM_SPLIT", "1")
+    monkeypatch.setenv("FP8T_GEMM_WGS", "9")
+    monkeypatch.setenv("FP8T_GEMM_VERBOSE", "1")
+    rng = np.random.default_rng(988)
+    M, N, K, CL = 200, 130, 300, 16
+    A = p16(rng.standard_normal((M, K)))
+    B = p16(rng.standard_normal((K, N)))
+    A[150, :] = p16(rng.standard_normal(K) * row_scale)
+    say(f"chunk_gemm_p16 guard rows tile={tile} scale={row_scale}")
+    got = gemm16(dev(A), dev(B), M, N, K, CL, 0, 0)
+    ran(capfd, tile)
+    assert np.array_equal(got, oracle.chunk_gemm_p16(A, B, CL))
+
+
 @pytest.mark.parametrize("tile", ["12", "13", "14", "15", "16", "17"])
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
 def test_p16_gemm_chunk_per_wave(tile, ta, tb, monkeypatch):
