@@ -136,8 +136,8 @@ __device__ __forceinline__ void stage(float* lds, int pitch, int lane, uint64_t 
 // chunks before).
 constexpr int kP16Dom = -110;
 
-// 2^96-scaled value of a finite code in bits 16-31 / 0-15 of w (an Inf or NaN
-// code comes out as 2^128 2^-96 or more, which fails the guard): the code's
+// Value times 2^-96 of a finite code in bits 16-31 / 0-15 of w (an Inf or NaN
+// code comes out as 2^32 2^-96 or more, which fails the guard): the code's
 // fields moved into FP32's, its subnormals onto FP32's.
 __device__ __forceinline__ float code_hi(uint32_t w) {
     return __uint_as_float((uint32_t)((int32_t)w >> 2) & 0x9FFFC000u);
@@ -356,7 +356,7 @@ void chunk_gemm_cpar(GemmArgs g, Plan p) {
         // turn: while one is computed on, the next is staged into the other
         // buffer and the one after it is on its way from memory.
         int fc = c0 + wave;                              // chunk and k of the fetched slab
-        int fk = fc * g.CL, fend = 0;
+        int fk = 0, fend = 0;                            // (a chunk past the last has no k in range)
         bool more = fc < c1;
         auto chunk_end = [&](int c) __attribute__((always_inline)) {
             const int kbeg = c * g.CL;
@@ -378,6 +378,7 @@ void chunk_gemm_cpar(GemmArgs g, Plan p) {
         int done_slabs = 0;
         int buf = 0;
         if (more) {
+            fk = fc * g.CL;
             fend = chunk_end(fc);
             fetch(fk);
             stage_slab(region[wave][0]);
