@@ -582,21 +582,25 @@ void chunk_gemm_valu(GemmArgs g, Plan p) {
                     }
                 } else {
                     const bool fresh = crem == g.CL;
-                    auto one = [&](int q) __attribute__((always_inline)) {
-                        float a[TM], b[TN];
-                        lds_read(a, b, buf, q);
-                        if (q == kk && fresh) first_step(vsplit, a, b);
-                        else fma_step(vsplit, a, b);
-                    };
-                    if constexpr (P16) {
+                    if constexpr (P16 && TM * TN > 1) {
                         // not unrolled: three roundings of a product (and four
                         // k of each) spilled up to 157 registers, 110 now
                         // (2048 x 2048 x 2048, CL 2048, 128 x 64 tiles: 1191
                         // -> 1015 us)
 #pragma clang loop unroll(disable)
-                        for (int q = kk; q < kk + seg; ++q) one(q);
+                        for (int q = kk; q < kk + seg; ++q) {
+                            float a[TM], b[TN];
+                            lds_read(a, b, buf, q);
+                            if (q == kk && fresh) first_step(vsplit, a, b);
+                            else fma_step(vsplit, a, b);
+                        }
                     } else {
-                        for (int q = kk; q < kk + seg; ++q) one(q);
+                        for (int q = kk; q < kk + seg; ++q) {
+                            float a[TM], b[TN];
+                            lds_read(a, b, buf, q);
+                            if (q == kk && fresh) first_step(vsplit, a, b);
+                            else fma_step(vsplit, a, b);
+                        }
                     }
                 }
                 kk += seg;
