@@ -144,8 +144,10 @@ __device__ __forceinline__ uint32_t fp16_code(float x) {
 // a multiple of 2^13, hence even, so s's even neighbour is hi's even neighbour.
 // (Subtracting is what makes it exact: with 1 + 2^14 the sum can leave the
 // binade at its top, where ulp(s) doubles.)  Valid while x 2^14 does not
-// overflow and x / 2^14 stays normal -- for the guarded paths (|x| in [2^-39,
-// 2^31] or 0) always; zero gives +0.  Equality with integer
+// overflow and x / 2^14 stays normal -- for plain FP16 sums (|x| in [2^-39,
+// 2^31] or 0) always -- and, with x scaled by 2^-110 (gemm_cpar_impl.h), where
+// FP16's subnormals are FP32's: sums below 2^-30 are multiples of 2^-39, 2^-149
+// scaled, of at most 9 bits, and pass through.  Zero gives +0.  Equality with integer
 // round-to-nearest-even is checked exhaustively over whole binades of both
 // signs in the tests.
 __device__ __forceinline__ float rn16v(float x) {

@@ -193,8 +193,8 @@ VALU_TILES = ["auto", "0", "1", "2", "3", "4", "5", "6", "7", "8", "9"]
 @pytest.mark.parametrize("tile", VALU_TILES)
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
 def test_chunk_gemm_exact_matches_oracle(tile, ta, tb, guard, monkeypatch):
-    """Both paths of the exact kernel (guarded: plain values with Veltkamp
-    rounding; safe: scaled by 2^96 with integer rounding) on every tile."""
+    """Both paths of the exact kernel (guarded: plain values rounded by a
+    multiplication and an FMA; safe: scaled by 2^96 with integer rounding) on every tile."""
     if tile != "auto":
         monkeypatch.setenv("FP8T_VALU_TILE", tile)
     monkeypatch.setenv("FP8T_GEMM_GUARD", guard)

@@ -167,8 +167,9 @@ def test_chains_stay_within_9x_the_sum_of_magnitudes():
 
 
 def veltkamp10(x):
-    """The guarded kernels' rounding: c = x (2^14 + 1); hi = c - (c - x), in
-    float32 arithmetic (numpy rounds to nearest even, as the VALU does)."""
+    """Veltkamp splitting, c = x (2^14 + 1); hi = c - (c - x), in float32
+    arithmetic (numpy rounds to nearest even, as the VALU does): the rounding
+    of products of FP16 operands on the register tiles."""
     c = (x * np.float32(16385.0)).astype(np.float32)
     d = (c - x).astype(np.float32)
     return (c - d).astype(np.float32)
@@ -184,3 +185,24 @@ def test_veltkamp_keeps_fp16_subnormal_sums():
     # and they are FP16 values: RN16 leaves them alone
     assert np.array_equal(oracle.p16_value(oracle.rn16(x.astype(np.float64))),
                           x.astype(np.float64))
+
+
+def two_step10(x):
+    """The guarded kernels' rounding of sums: s = x (1 - 2^14), hi = fma(x,
+    2^14, s) (exact in float64, then rounded to float32)."""
+    s = (x * np.float32(-16383.0)).astype(np.float32)
+    return (x.astype(np.float64) * 16384.0 + s.astype(np.float64)).astype(np.float32)
+
+
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -110])
+def test_two_step_rounding_keeps_fp16_subnormal_sums(scale):
+    """FP16-subnormal sums (m 2^-39, m < 512) pass through, plain and in the
+    2^-110 domain, where they are FP32 subnormals."""
+    m = np.arange(512, dtype=np.float64)
+    x = (m * 2.0 ** -39 * scale).astype(np.float32)
+    assert np.array_equal(x.astype(np.float64) / (2.0 ** -39 * scale), m)
+    for s in (1.0, -1.0):
+        y = np.float32(s) * x
+        got = two_step10(y)
+        assert np.array_equal(got, y)
+        assert not np.signbit(got[0])       # a zero sum is +0

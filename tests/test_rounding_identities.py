@@ -19,8 +19,8 @@ def veltkamp10(x):
 
 
 def test_veltkamp_split_is_round_to_nearest_even_on_whole_binades():
-    """Exhaustive over every significand of binades spanning the exact GEMM's
-    guarded domain (unscaled FP16 values: normal from 2^-30 up to the 2^31
+    """Veltkamp splitting (the FP16 products of the register tiles round with
+    it), exhaustive over every significand of binades spanning the guarded domain (unscaled FP16 values: normal from 2^-30 up to the 2^31
     bound of the guard), both signs; ties (frequent for sums of FP8 products)
     must go to even."""
     m = np.arange(1 << 23, dtype=np.uint32)
