@@ -723,6 +723,40 @@ def test_chunk_gemm_guard_falls_back_per_piece(monkeypatch):
         assert np.array_equal(Cg, Co), np.argwhere(Cg != Co)[:5]
 
 
+@pytest.mark.parametrize("tile", ["1", "3", "4", "5", "6", "7", "8"])
+@pytest.mark.parametrize("split", ["0", "1"])
+def test_chunk_gemm_guard_falls_back_on_register_tiles(tile, split, monkeypatch):
+    """test_chunk_gemm_guard_falls_back_per_piece on each register tile (the
+    planner gives these sizes to the chunk-per-wave kernel), whole and shared
+    tiles, operands and results at odd addresses with odd leading dimensions."""
+    monkeypatch.setenv("FP8T_VALU_TILE", tile)
+    monkeypatch.setenv("FP8T_GEMM_SPLIT", split)
+    if split == "1":
+        monkeypatch.setenv("FP8T_GEMM_WGS", "7")
+    rng = np.random.default_rng(572)
+    M, N, K, CL = 150, 140, 768, 64
+    A, B = _operands(rng, M, N, K, 0, 0)
+    A[5, :] = 0x7B
+    A[100, 700] = 0xFC
+    A[17, 3] = 0x7F
+    B[:, 3] = np.where(rng.random(K) < 0.5, 0x7A, 0xFA)
+    A[40, :] = 0x01
+    lda, ldb, ldc = K + 3, N + 5, N + 1
+    Ap, Bp = np.full(1 + M * lda, 0x7F, np.uint8), np.full(3 + K * ldb, 0x7F, np.uint8)
+    Ap[1:].reshape(M, lda)[:, :K] = A
+    Bp[3:].reshape(K, ldb)[:, :N] = B
+    C = torch.zeros((M, ldc), dtype=torch.uint16, device=DEV)
+    wb = fp8t.chunk_gemm_workspace_size(0, 0, M, N, K, CL, fp8t.EXACT)
+    ws = torch.empty(wb, dtype=torch.uint8, device=DEV) if wb else None
+    assert (wb > 0) == (split == "1")
+    say(f"guard fallback on a register tile: tile={tile} split={split}")
+    fp8t.chunk_gemm(0, 0, M, N, K, CL, dev(Ap)[1:], lda, dev(Bp)[3:], ldb, C, ldc, fp8t.EXACT, ws, wb)
+    got = host(C)
+    Co = oracle.chunk_gemm(A, B, CL)
+    assert np.array_equal(got[:, :N], Co), np.argwhere(got[:, :N] != Co)[:5]
+    assert not got[:, N:].any()
+
+
 @pytest.mark.parametrize("tile", ["auto", "4", "9", "11"])
 @pytest.mark.parametrize("CL", [64, 1024])
 @pytest.mark.parametrize("b0", [0x50, 0x52, 0x56])

@@ -20,8 +20,9 @@ def veltkamp10(x):
 
 def test_veltkamp_split_is_round_to_nearest_even_on_whole_binades():
     """Veltkamp splitting (the FP16 products of the register tiles round with
-    it), exhaustive over every significand of binades spanning the guarded domain (unscaled FP16 values: normal from 2^-30 up to the 2^31
-    bound of the guard), both signs; ties (frequent for sums of FP8 products)
+    it), exhaustive over every significand of binades spanning the guarded
+    domain (unscaled FP16 values: normal from 2^-30 up to the 2^31 bound of the
+    guard), both signs; ties (frequent for sums of FP8 products)
     must go to even."""
     m = np.arange(1 << 23, dtype=np.uint32)
     for e in (127 - 30, 127 - 1, 127, 127 + 30):
