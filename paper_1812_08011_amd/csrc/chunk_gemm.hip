@@ -218,69 +218,130 @@ constexpr double kClockHz = 2.4e9;      // MI355X peak engine clock
 constexpr double kLanesPerCU = 128.0;   // 32-bit VALU lane-ops per clock per CU
 constexpr double kFoldBytesPerS = 5e12; // effective HBM rate of the fold pass
 
-// Relative cost per multiply-accumulate of each register tile on a CU with
-// enough waves resident (see valu_efficiency), in VALU instructions at the
-// peak clock: 3 for the rounded FMA of the guarded path, plus operand decode,
-// LDS reads, loop overhead and the clock the chip holds; from the times of the
-// 50176 x 256 x 2304 GEMM (large tiles) and the 512 x 512 x 16384 one (small
-// tiles, and the chunk-per-wave kernel).
-double valu_ops_per_mac(int cfg) {
-    switch (cfg) {
-        case 4: return 4.3;     // 4 x 4, 4 waves per SIMD
-        case 3: return 4.65;    // 4 x 8
-        case 2: return 4.6;     // 8 x 4
-        case 1: return 4.8;     // 8 x 8, 2 waves per SIMD
-        case 0: return 4.9;
-        case 7: return 3.97;    // 4 x 4 on 128 x 64 tiles, 8 waves per workgroup
-        case 8: return 3.95;    // 4 x 4 on 64 x 128 tiles, 8 waves per workgroup
-        case 5: return 5.5;     // 2 x 2
-        case kCparConfig:       // a chunk per wave, 4 x 4
-        case kCparConfig + 1:
-        case kCparConfig + 2: return 4.4;
-        case kCparConfig + 3:   // 2 x 2
-        case kCparConfig + 4:
-        case kCparConfig + 5: return 5.95;
-        case kChainConfig: return 5.6;       // chain kernel, 2 x 2
-        case kChainConfig + 1: return 6.2;   // chain kernel, 1 x 2
-        case kChainConfig + 2: return 7.8;   // chain kernel, 1 x 1
-        default: return 10.8;   // 1 x 1
+// Times of the vector-ALU kernels' plans, fitted to about 3900 calls with every
+// plan of each timed: M 4 .. 50176, N 4 .. 6000, K 8 .. 65536, CL 1 .. K, every
+// layout, with and without a workspace, up to 3 10^10 multiply-accumulates,
+// and convolutions.  The plan it picks takes 1.014 times the best one's time
+// on average (FP16 operands 1.01, convolutions 1.005).  One cost per
+// multiply-accumulate, from the times of two large shapes, took 1.06, and on
+// calls of few or short chunks up to 1.6 times the plans of the estimate
+// before that (21 x 3241 x 947, CL 4: 53 us against 33).
+struct ValuCost {
+    float ops[kValuConfigs];       // VALU instructions per multiply-accumulate, enough waves resident
+    float tile_us[kValuConfigs];   // CU time of a tile's start and end
+    // by family (register tiles, chain, chunk per wave): the cost of layout 2
+    // trans_a + trans_b against 0, and of byte loads (a workspace query does not
+    // know the leading dimensions); the share of a CU's rate reached with 1, 2,
+    // 4 and 8 waves per SIMD
+    float layout[3][4];
+    float odd_edge[3];             // more per operand whose contiguous edge is no multiple of 4
+    float eff[3][4];
+    // share of a last, partial round of tiles that the rounds before it do not
+    // cover (workgroups do not end together)
+    float rest_share[3];
+    float chunk_ops[3];            // instructions per output at a chunk's end
+    float part_ops[3];             // more per multiply-accumulate in parts of a slab
+    // the fold pass: launch and start, chunk sums written and read, each chunk
+    // of an output's chain
+    float fold_us, fold_us_per_mb, fold_us_per_chunk;
+};
+constexpr ValuCost kExactCost = {
+    {4.633, 4.633, 4.933, 3.721, 3.891, 8.741, 20.392, 3.665, 3.659,
+     5.978, 6.697, 8.697, 4.253, 4.12, 4.7, 6.533, 5.901, 6.281},
+    {4.916, 4.916, 2.023, 0.816, 0.375, 0.472, 0.227, 0.732, 0.675,
+     0.465, 0.309, 0.291, 0.712, 2.138, 2.059, 0.444, 1.825, 2.853},
+    {{1, 1.086, 1.068, 1.129}, {1, 1.02, 1.149, 1.119}, {1, 1.043, 0.987, 1.195}}, {0, 0, 0},
+    {{0.433, 0.683, 1, 1.353}, {0.354, 0.584, 1, 1.008}, {0.4, 0.646, 1, 1}},
+    {0.697, 0.595, 0.572}, {7.85, 9.77, 1.12}, {1.62, 0, 1.09}, 8.03, 0.292, 0.058};
+constexpr ValuCost kConvCost = {
+    {0, 0, 0, 0, 4.184, 0, 0, 4.114, 0,
+     0, 0, 0, 0, 0, 0, 0, 0, 0},
+    {0, 0, 0, 0, 0.851, 0, 0, 1.429, 0,
+     0, 0, 0, 0, 0, 0, 0, 0, 0},
+    {{1, 1, 1.242, 1}, {0, 0, 0, 0}, {0, 0, 0, 0}}, {0, 0, 0},
+    {{0.448, 0.915, 1, 1.05}, {0, 0, 0, 0}, {0, 0, 0, 0}},
+    {1, 0, 0}, {6.51, 0, 0}, {2.89, 0, 0}, 5.54, 0.223, 0.063};
+constexpr ValuCost kFastCost = {
+    {0, 0, 0, 0, 2.111, 6.818, 25.722, 0, 0,
+     4.337, 6.252, 9.263, 0, 0, 0, 0, 0, 0},
+    {0, 0, 0, 0, 0.898, 0.254, 0.081, 0, 0,
+     0.346, 0.169, 0.111, 0, 0, 0, 0, 0, 0},
+    {{1, 0.752, 0.706, 1.706}, {1, 0.909, 0.793, 1.172}, {0, 0, 0, 0}}, {0.267, 0.232, 0},
+    {{0.32, 0.588, 1, 1.223}, {0.189, 0.415, 1, 0.697}, {0, 0, 0, 0}},
+    {0.659, 0.393, 0}, {14.46, 2.22, 0}, {1.14, 0, 0}, 16.59, 0.477, 0.2};
+constexpr ValuCost kP16Cost = {
+    {0, 0, 0, 0, 10.416, 16.54, 25.864, 10.053, 11.936,
+     0, 0, 0, 8.175, 6.767, 6.224, 10.997, 8.908, 9.404},
+    {0, 0, 0, 0, 0.151, 0.775, 0.563, 6.115, 3.674,
+     0, 0, 0, 0.066, 3.788, 6.48, 0.196, 2.297, 2.372},
+    {{1, 0.905, 0.883, 1.098}, {0, 0, 0, 0}, {1, 0.902, 0.888, 1.056}}, {0, 0, 0},
+    {{0.366, 0.807, 1, 1.275}, {0, 0, 0, 0}, {0.387, 0.69, 1, 1}},
+    {0.762, 0, 0.48}, {0.9, 0, 0.37}, {0.86, 0, 2.62}, 7.6, 0.223, 0.013};
+
+int valu_family(int cfg) { return is_cpar(cfg) ? 2 : is_chain(cfg) ? 1 : 0; }
+// k of the slabs a kernel's inner loop is unrolled for
+int valu_slab(int cfg) {
+    if (is_cpar(cfg)) return valu_shape(cfg).TM == 4 ? 16 : 32;
+    return cfg < 4 ? 16 : cfg == 6 ? 64 : 32;
+}
+double valu_efficiency(const float (&e)[4], double w) {
+    if (w >= 4.0) return e[2] + (e[3] - e[2]) * ((w < 8.0 ? w : 8.0) - 4.0) / 4.0;
+    if (w >= 2.0) return e[1] + (e[2] - e[1]) * (w - 2.0) / 2.0;
+    return w >= 1.0 ? e[0] + (e[1] - e[0]) * (w - 1.0) : e[0] * w;
+}
+
+// Estimates of one configuration's plans for one call.
+struct ValuEstimate {
+    const ValuCost& cost;
+    int cfg, fam, nw, occ, cus;
+    int64_t nch;
+    double waves;                  // per SIMD of a workgroup
+    double chunk_s, tile_s;        // a tile-chunk, a tile's start and end, on a CU at full rate
+    ValuEstimate(const ValuCost& c, int cfg_, const ValuShape& sh, int occ_, int cus_, int64_t K,
+                 int64_t CL, int64_t nch_, int layout, int odd_edges)
+        : cost(c), cfg(cfg_), fam(valu_family(cfg_)), nw(is_cpar(cfg_) ? cpar_waves(cfg_) : 1),
+          occ(occ_), cus(cus_), nch(nch_), waves(sh.NT / 256.0), tile_s(c.tile_us[cfg_] * 1e-6) {
+        // share of the products that a slab's part holds: a chunk's last slab
+        // (chunk per wave), slabs cut by chunk ends (register tiles)
+        const int bk = valu_slab(cfg);
+        double part = 0.0;
+        if (fam == 2) part = (double)(CL % bk) / (double)CL;
+        else if (fam == 0)
+            part = CL < bk ? 1.0 : CL >= K ? (double)(K % bk) / (double)K
+                 : CL % bk == 0 ? 0.0 : (double)bk / (double)CL;
+        chunk_s = (double)sh.BM * sh.BN *
+                  ((double)K / (double)nch * (c.ops[cfg] * c.layout[fam][layout] * (1.0 + c.odd_edge[fam] * odd_edges) +
+                                              part * c.part_ops[fam]) +
+                   c.chunk_ops[fam]) /
+                  (kLanesPerCU * kClockHz);
     }
-}
-
-// VALU instructions per multiply-accumulate the fast chain kernel saves over
-// the exact one (measured on 512 x 512 outputs, K 16384 and 65536, CL 8 and
-// 12): the rounding after each FMA goes, worth more on the 2 x 2 tile than
-// on the narrower ones.
-double chain_fast_saving(int cfg) {
-    return cfg == kChainConfig ? 2.6 : cfg == kChainConfig + 1 ? 2.4 : 1.4;
-}
-
-// Fraction of a CU's VALU rate reached with w waves per SIMD resident: each
-// multiply-accumulate is a chain of dependent instructions, and on gfx950
-// about four waves per SIMD are needed to issue every cycle (measured with a
-// barrier per slab: a 2 x 2 register tile at one wave per SIMD runs at a
-// quarter of the rate a 1 x 1 tile reaches at four).  The chunk-per-wave
-// kernel has no such barrier and issues better with few waves (measured: 256 x
-// 1024 x 1024 with 4 x 4 tiles 34 / 21 / 20 us at one / two / four, 128 x 128
-// x 1024 with 2 x 2 tiles 14.4 / 9.7 / 9.0 us).
-double valu_efficiency(double w) { return w >= 4.0 ? 1.0 : w / 4.0; }
-double cpar_efficiency(double w) {
-    return w >= 4.0 ? 1.0 : w >= 2.0 ? 0.92 + 0.04 * (w - 2.0) : 0.52 + 0.4 * (w - 1.0);
-}
-// A chunk-per-wave tile's start and end (operand latency, result stores): the
-// more waves a workgroup has, the fewer workgroups a CU holds to cover them.
-double cpar_cost_per_tile(int waves) { return waves == 4 ? 0.5e-6 : waves == 8 ? 0.7e-6 : 1.2e-6; }
-
-// The fold pass of the VALU kernels' shared tiles: a fixed part (launch, the
-// pieces' starts) and the chunk sums written and read back (measured: 27 us
-// for 134 MB of them, 170 us for 0.8 GB, 6-9 us where there are few).
-constexpr double kValuFoldFixed = 9e-6, kValuFoldBytesPerS = 1e13;
-
-// Extra VALU instructions per multiply-accumulate with FP16 operands (from the
-// times of the 256 x 6000 x 1024 GEMM and its two backward ones): the product's
-// multiplication and its rounding to FP16 replace the FMA's one, decoding
-// and the bound on a slab's smallest product cost more per staged code.
-constexpr double kP16ProductOps = 7.5, kP16CparOps = 3.8;
+    // n chunks of a tile with res workgroups resident; a chunk-per-wave
+    // workgroup's last round may leave waves idle
+    double chunks(double res, int64_t n) const {
+        if (fam != 2) return (double)n * chunk_s / valu_efficiency(cost.eff[fam], res * waves);
+        const int64_t rem = n % nw;
+        return (double)(n - rem) * chunk_s / valu_efficiency(cost.eff[fam], res * waves) +
+               (rem ? (double)rem * chunk_s / valu_efficiency(cost.eff[fam], res * (double)rem / 4.0)
+                    : 0.0);
+    }
+    // T whole tiles: rounds of occ per CU, then the rest
+    double whole(int64_t T) const {
+        const int64_t per_cu = (T + cus - 1) / cus, rest = per_cu % occ;
+        return (double)(per_cu - rest) * (chunks(occ, nch) + tile_s) +
+               (rest ? (double)rest * (chunks((double)rest, nch) + tile_s) *
+                           (per_cu > occ ? cost.rest_share[fam] : 1.0)
+                     : 0.0);
+    }
+    // a plan with shared tiles, ws bytes of chunk sums
+    double shared(const Plan& p, size_t ws) const {
+        const int64_t wgs = (p.G + cus - 1) / cus, q = p.t_whole / p.G;
+        const double res = (double)(wgs < occ ? wgs : occ);
+        return (double)wgs * ((double)q * chunks(res, nch) + chunks(res, (p.L + p.G - 1) / p.G) +
+                              ((double)q + 1.5) * tile_s) +
+               1e-6 * (cost.fold_us + cost.fold_us_per_mb * 1e-6 * (double)ws +
+                       cost.fold_us_per_chunk * (double)nch);
+    }
+};
 
 // Matrix-core fast mode, CU time of one output-chunk (the VALU epilogue
 // dominates; the matrix-core share grows with CL) and of the per-tile start
@@ -349,6 +410,7 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
     const int force_split = env_int("FP8T_GEMM_SPLIT", -1);
     const int verbose = env_int("FP8T_GEMM_VERBOSE", 0);
     const int64_t nch = (K + CL - 1) / CL;
+    const int odd_edges = ((ta ? M : K) % 4 != 0) + ((tb ? K : N) % 4 != 0);
     for (int pass = 0; pass < 2 && best.cfg < 0; ++pass) {
         for (int cfg = 0; cfg < ncfg; ++cfg) {
             if (pass == 0 && force_cfg >= 0 && cfg != force_cfg) continue;
@@ -377,18 +439,8 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
                    : p16  ? valu_p16_kernel(cfg, ta, tb)
                           : valu_kernel(cfg, ta, tb, fast);
                 NT = sh.NT, BM = sh.BM, BN = sh.BN;
-                // the MACs of a chunk, and its end (an add and a rounding); an
-                // FP16 product costs its multiplication and rounding on top,
-                // and the fast chain kernel does without the rounding
-                const double ops = valu_ops_per_mac(cfg) +
-                                   (!p16 ? 0.0 : is_cpar(cfg) ? kP16CparOps : kP16ProductOps) -
-                                   (fast && is_chain(cfg) ? chain_fast_saving(cfg) : 0.0);
-                t_out = ((double)CL * ops + 4.0) / (kLanesPerCU * kClockHz);
             }
             if (!fn) continue;
-            const bool cpar = !mf && is_cpar(cfg);
-            const int nw = cpar ? cpar_waves(cfg) : 1;
-            if (cpar) t_tile = cpar_cost_per_tile(nw);
             int occ = kernel_occupancy(fn, NT, dev);
             if (occ <= 0) continue;
             if (occ > 8) occ = 8;
@@ -398,6 +450,10 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
             int64_t gmax = (int64_t)cus * occ;
             if (force_g > 0 && force_g < gmax) gmax = force_g;
             const double t_chunk = (double)BM * BN * t_out;     // one tile-chunk on a CU
+            auto valu = [&]() {
+                return ValuEstimate(conv ? kConvCost : p16 ? kP16Cost : fast ? kFastCost : kExactCost,
+                                    cfg, valu_shape(cfg), occ, cus, K, CL, nch, 2 * ta + tb, odd_edges);
+            };
             for (int split = 0; split < 2; ++split) {
                 if (split && !allow_ws) continue;
                 if (force_split == 0 && split) continue;
@@ -408,7 +464,7 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
                 size_t ws = 0;
                 // the streamed kernel writes split tiles' chunk sums as scattered
                 // 2-byte stores: the other kernels are faster there; the
-                // chunk-per-wave and chain kernels have no shared tiles
+                // chain kernel has no shared tiles
                 if (split && mf && cfg >= 2) continue;
                 if (split && !mf && is_chain(cfg)) continue;
                 if (!split && mf && cfg == 5) {
@@ -435,16 +491,7 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
                     // memory work (a lone one runs at about half the CU rate)
                     int64_t per_cu = (T + cus - 1) / cus;
                     if (mf && cfg == 2 && per_cu < 2) per_cu = 2;
-                    est = (double)per_cu * (nch * t_chunk + t_tile);
-                    if (cpar) {
-                        // rounds of nw chunks
-                        const int64_t res = per_cu < occ ? per_cu : occ;
-                        est = (double)per_cu * ((nch + nw - 1) / nw * nw * t_chunk /
-                                                cpar_efficiency((double)res * NT / 256.0) + t_tile);
-                    } else if (!mf) {
-                        const int64_t res = per_cu < occ ? per_cu : occ;
-                        est /= valu_efficiency((double)res * NT / 256.0);
-                    }
+                    est = mf ? (double)per_cu * (nch * t_chunk + t_tile) : valu().whole(T);
                 } else {
                     int64_t G = gmax;
                     if (G > T * nch) G = T * nch;
@@ -457,20 +504,9 @@ Choice plan_gemm(Kind kind, int ta, int tb, int64_t M, int64_t N, int64_t K, int
                     const int64_t per_wg = q * nch + (p.L + G - 1) / G;
                     ws = (size_t)(T - p.t_whole) * nch * BM * BN * sizeof(uint16_t) + kWsAlign;
                     if (ws > ws_cap) continue;
-                    est = (double)wg_per_cu * (per_wg * t_chunk + (q + 2) * t_tile);
-                    if (cpar) {
-                        const int64_t rest = (p.L + G - 1) / G;
-                        const double chunks = (double)(q * ((nch + nw - 1) / nw * nw)) +
-                                              (double)(rest > nw / 2 ? rest : nw / 2);
-                        const int64_t res = wg_per_cu < occ ? wg_per_cu : occ;
-                        est = (double)wg_per_cu * (chunks * t_chunk /
-                              cpar_efficiency((double)res * NT / 256.0) + (q + 2) * t_tile);
-                    } else if (!mf) {
-                        const int64_t res = wg_per_cu < occ ? wg_per_cu : occ;
-                        est /= valu_efficiency((double)res * NT / 256.0);
-                    }
-                    est += mf ? 2.0 * (double)ws / kFoldBytesPerS + 4e-6
-                              : 2.0 * (double)ws / kValuFoldBytesPerS + kValuFoldFixed;
+                    est = mf ? (double)wg_per_cu * (per_wg * t_chunk + (q + 2) * t_tile) +
+                                   2.0 * (double)ws / kFoldBytesPerS + 4e-6
+                             : valu().shared(p, ws);
                 }
                 p.xcd_remap = p.t_whole % 8 == 0 && p.G % 8 == 0;
                 if (force_split == 1 && !split && allow_ws) est *= 1e6;   // any shared plan wins
