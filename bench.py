@@ -46,18 +46,18 @@ FP8_MFMA_MAC_S = 5.0e15 / 2                             # dense FP8 5.0 PFLOP/s
 # HBM traffic of the exact-mode chunk_gemm calls of one step, from two
 # rocprofv3 counter passes (FETCH_SIZE, WRITE_SIZE) over this benchmark,
 # calibrated by the counters of a plain device copy of known size (fetch x2.0,
-# write x1.0); average calibrated bytes per call (forward 190.2 MB,
-# backward-data 293.9 MB, weight-gradient 547.4 MB including the chunk sums
+# write x1.0); average calibrated bytes per call (forward 189.8 MB,
+# backward-data 260.6 MB, weight-gradient 547.5 MB including the chunk sums
 # of its shared tiles and the fold pass).  Valid only for the kernel sources
 # they were measured on (EXACT_KERNEL_SOURCES): any change to them reports null.
-TRAFFIC_SOURCES_SHA256 = "4dc6d8852e35dced7cb4e441e5b27a6295d2749a09e4a6bf8087a7f8e0c49030"
-EXACT_TRAFFIC_BYTES_PER_CALL = 343.8e6
+TRAFFIC_SOURCES_SHA256 = "6f59c25ead8820a8be191da5fb0c0d9855b0da7d64223d0f88acfbc9c0178602"
+EXACT_TRAFFIC_BYTES_PER_CALL = 332.6e6
 
 
 # The sources that decide what an exact-mode chunk_gemm call runs: the VALU
 # kernel, its instantiations, the planner and fold pass, the shared device code.
 EXACT_KERNEL_SOURCES = ("chunk_gemm.hip", "fp8t_device.h", "fp8t_host.h", "gemm_plan.h",
-                        "gemm_chain.hip", "gemm_cpar_impl.h", "gemm_cpar_nn.hip",
+                        "gemm_chain.hip", "gemm_conv_words.h", "gemm_cpar_impl.h", "gemm_cpar_nn.hip",
                         "gemm_cpar_nt.hip", "gemm_cpar_tn.hip", "gemm_cpar_tt.hip",
                         "gemm_valu.h", "gemm_valu.hip", "gemm_valu_impl.h",
                         "gemm_valu_nn.hip", "gemm_valu_nt.hip", "gemm_valu_tn.hip",
@@ -79,35 +79,37 @@ def kernel_sources_sha256():
 def exact_peak_mac_s(cl):
     """Emulation ceiling of one exact-mode multiply-accumulate: gfx950 has no
     adder for the paper's FP16, so a MAC costs one FP32 FMA plus two more VALU
-    ops that round the result to a 10-bit significand, and each chunk end
-    adds one more add + rounding (3 ops) per output.  Priced at
-    the chip's full VALU rate."""
-    return VALU_LANE_OPS / (3.0 + 3.0 / cl)
+    ops that round the result to a 10-bit significand -- but for a chunk's
+    first product, an FP16 value -- and each chunk end adds one more add +
+    rounding (3 ops) per output: 3 CL + 1 per chunk.  Priced at the chip's full
+    VALU rate."""
+    return VALU_LANE_OPS / (3.0 + 1.0 / cl)
 
 
 def fast_peak_mac_s(cl):
-    """Fast mode: min(FP8 MFMA peak, VALU epilogue of 6 ops per output per
-    chunk: round (2), add, round (2), running maximum)."""
-    return min(FP8_MFMA_MAC_S, VALU_LANE_OPS * cl / 6.0)
+    """Fast mode: min(FP8 MFMA peak, VALU epilogue of 5.5 ops per output per
+    chunk: round (2), add, round (2), and the running maximum, one three-input
+    instruction per two outputs)."""
+    return min(FP8_MFMA_MAC_S, VALU_LANE_OPS * cl / 5.5)
 
 
 def sr_gemm_peak_mac_s():
     """ALU ceiling of chunk_gemm_sr: per multiply-accumulate one FP32 FMA, the
     stochastic rounding (an add and an and on the raw bits) and the uniform's
     extraction (a shift, or a half-rate bit-field extract: 1.5 on average), plus
-    1/8 of a Philox4x32-10 block (20 64-bit multiplies at half rate, 20
-    three-input xors, 4 complements = 64 full-rate slots): 12.5 full-rate VALU
-    slots per MAC."""
-    return VALU_LANE_OPS / 12.5
+    1/32 of a thread's four Philox4x32-10 blocks for two k, which share work in
+    their first rounds (65 64-bit multiplies at half rate and 56 three-input
+    xors = 186 full-rate slots): 10.3 full-rate VALU slots per MAC."""
+    return VALU_LANE_OPS / (4.5 + 186.0 / 32.0)
 
 
 def p16_peak_mac_s(cl):
     """ALU ceiling of chunk_gemm_p16 (FP16 operands): per multiply-accumulate
     the product's rounding to FP16 (a multiply by the pre-split operand and an
     FMA), the add into the chunk sum and its rounding (multiply, FMA): 5 VALU
-    ops, plus the chunk end's 3 per output.  Priced at the chip's full VALU
-    rate."""
-    return VALU_LANE_OPS / (5.0 + 3.0 / cl)
+    ops, 2 for a chunk's first product, plus the chunk end's 3 per output: 5 CL
+    per chunk.  Priced at the chip's full VALU rate."""
+    return VALU_LANE_OPS / 5.0
 
 
 def parse():
