@@ -18,8 +18,8 @@
 // XOR-swizzled by the row through the lanes' fetch addresses.  A wave whose
 // block fails the guard (running sums at 2^31 or NaN) forms it again from the
 // same operands with the 2^96-scaled epilogue.
-// Bound by the result stores and the epilogue on the vector ALUs (each about
-// 45 us of the first shape below), which workgroups of different age overlap
+// Bound by the result stores and the epilogue on the vector ALUs (about 44 and
+// 32 us of the first shape below), which workgroups of different age overlap
 // in part.  Measured (us, chunk_gemm_mfma_wave / RB = 1 / RB = 2), M x N x K,
 // CL 64: 50176 x 2304 x 256 114 / 102 / 94 (2.5 TB/s of results), 50176 x 576
 // x 64 55 / 14.9 / 14.0, 25088 x 1728 x 192 83 / 36.9 / 33.4, 12544 x 1152 x

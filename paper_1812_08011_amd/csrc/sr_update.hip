@@ -53,7 +53,8 @@ __device__ __forceinline__ void update_one(uint32_t wc, uint32_t gc, uint32_t vc
 // held in vector registers, as the three-input xor issues at half rate with a
 // scalar operand.  Measured at 25.6 M parameters: ADAM with the second moments
 // of 1e-4 gradients (many pairs on the general path, which takes the same
-// block) 179 -> 168 us, SGD, bound by memory as well, 61.4 -> 60.7 us.
+// block) 179 -> 168 us; SGD, bound by memory as well, 61.4 against 60.7 us, which
+// is within what its runs differ by.
 struct PairPhilox {
     uint32_t a[8], b[8];              // keys of rounds 3 .. 10
     uint32_t z1, x2;                  // off_hi ^ key, lo(M1 off_lo) ^ key
