@@ -12,7 +12,7 @@
  *   P8  = the paper's FP8, (sign, exponent, mantissa) = (1, 5, 2)
  *   P16 = the paper's FP16, (1, 6, 9) -- not IEEE binary16
  * Readings where the paper is silent (bias, subnormals, specials, tie-break,
- * random source) are listed in the design doc and repeated at each function.
+ * random source) are stated at each function.
  *
  * All arithmetic that decides a result is exact: values are held as integers
  * in units of 2^-39 (the smallest P16 step) in 128-bit integers, and every
